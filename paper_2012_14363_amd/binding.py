@@ -1,10 +1,12 @@
-"""Thin ctypes binding over libtp_pack.so: same names as include/tp_pack.h, argument
-marshalling only.  Every step of the path runs inside the library; without the
-built library (or, for pack/unpack, without a GPU) calls fail loudly.
+"""Thin binding over libtp_pack.so: same names as include/tp_pack.h, argument
+marshalling only (ctypes; the pack/unpack calls themselves through the extension
+module _pycall, csrc/pycall.c).  Every step of the path runs inside the library; without
+the built library (or, for pack/unpack, without a GPU) calls fail loudly.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -65,15 +67,24 @@ class TpError(RuntimeError):
 
 
 _lib = None
+_PYCALL = __package__ + "._pycall"
+try:
+    _pycall = importlib.import_module(_PYCALL)
+except ImportError:   # not built yet: lib() says so, or finds it once it is
+    _pycall = None
 
 
 def lib() -> ctypes.CDLL:
     """The loaded library.  Raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _pycall
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
+        try:
+            _pycall = importlib.import_module(_PYCALL)
+        except ImportError:
+            _pycall = None
+        if not os.path.exists(LIB_PATH) or _pycall is None:
             raise RuntimeError(
-                f"{LIB_PATH} is missing: build it with `python -m paper_2012_14363_amd.build` "
+                f"{LIB_PATH} or the module _pycall beside it is missing: build them with `python -m paper_2012_14363_amd.build` "
                 "(there is no CPU or PyTorch fallback for the pack/unpack path)")
         # One HIP runtime per process: PyTorch ships its own libamdhip64.  Import it first so the
         # loader resolves this library's dependency to that already-loaded runtime; loaded the
@@ -129,6 +140,8 @@ def lib() -> ctypes.CDLL:
         L.tp_error_string.argtypes = [ctypes.c_int]
         L.tp_error_string.restype = ctypes.c_char_p
         _lib = L
+        _pycall.setup({name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}, _check, _first_stream,
+                      *_stream_getters())
     return _lib
 
 
@@ -226,45 +239,55 @@ def _ptr(buf) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _first_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
-def _pack_call(fn_name, inbuf, incount, t, outbuf, outsize, position, stream):
-    pos = ctypes.c_int64(position)
-    rc = getattr(lib(), fn_name)(_ptr(inbuf), incount, t, _ptr(outbuf), outsize, ctypes.byref(pos), _stream(stream))
-    _check(rc, fn_name)
-    return pos.value
+def _first_stream() -> int:
+    """The current stream's handle, with whatever torch has to set up for it (once per process)."""
+    import torch
+    return torch.cuda.current_stream().cuda_stream
 
 
-def _unpack_call(fn_name, inbuf, insize, position, outbuf, outcount, t, stream):
-    pos = ctypes.c_int64(position)
-    rc = getattr(lib(), fn_name)(_ptr(inbuf), insize, ctypes.byref(pos), _ptr(outbuf), outcount, t, _stream(stream))
-    _check(rc, fn_name)
-    return pos.value
+def _stream_getters():
+    """Functions for (current device index, that device's current stream handle) that build no objects: the pack
+    and unpack calls ask for the stream every time, and torch.cuda.current_stream() takes 2.6 us.  A torch
+    without them is asked the long way."""
+    try:
+        from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+    except ImportError:
+        return (lambda: 0), (lambda device: _first_stream())
+    return _cuda_getDevice, _cuda_getCurrentRawStream
 
 
-def pack(inbuf, incount: int, t: int, outbuf, outsize: int, position: int, stream=None) -> int:
-    """tp_pack; returns the new position."""
-    return _pack_call("tp_pack", inbuf, incount, t, outbuf, outsize, position, stream)
+def _late(name):
+    """A call of _pycall in a process that began before it was built."""
+    def call(*args, **kwargs):
+        lib()
+        return getattr(_pycall, name)(*args, **kwargs)
+    call.__name__ = name
+    return call
 
 
-def pack_async(inbuf, incount: int, t: int, outbuf, outsize: int, position: int, stream=None) -> int:
-    """tp_pack_async (enqueue only); returns the new position."""
-    return _pack_call("tp_pack_async", inbuf, incount, t, outbuf, outsize, position, stream)
-
-
-def unpack(inbuf, insize: int, position: int, outbuf, outcount: int, t: int, stream=None) -> int:
-    """tp_unpack; returns the new position."""
-    return _unpack_call("tp_unpack", inbuf, insize, position, outbuf, outcount, t, stream)
-
-
-def unpack_async(inbuf, insize: int, position: int, outbuf, outcount: int, t: int, stream=None) -> int:
-    """tp_unpack_async (enqueue only); returns the new position."""
-    return _unpack_call("tp_unpack_async", inbuf, insize, position, outbuf, outcount, t, stream)
+if _pycall is not None:
+    _pycall.on_first_use(lib)
+# pack, pack_async(inbuf, incount, t, outbuf, outsize, position, stream=None): new position
+# unpack, unpack_async(inbuf, insize, position, outbuf, outcount, t, stream=None): new position
+# pack_batch, pack_batch_async(batch, outbuf, outsize, position, stream=None): new position
+# unpack_batch, unpack_batch_async(inbuf, insize, position, batch, stream=None): new position
+# pack_host(inbuf, incount, t, host_outbuf, outsize, position, staging=None, staging_size=0, method=TP_METHOD_AUTO,
+#           stream=None): (new position, method used)
+# unpack_host(host_inbuf, insize, position, outbuf, outcount, t, staging=None, staging_size=0, method=TP_METHOD_AUTO,
+#             stream=None): (new position, method used)
+# pack_host_static(inbuf, incount, t, host_outbuf, outsize, position, stream=None): new position
+# Buffers are torch tensors (anything with data_ptr()) or raw addresses; stream is a torch stream, a raw
+# handle, or None for torch's current stream.
+(pack, pack_async, unpack, unpack_async, pack_batch, pack_batch_async, unpack_batch, unpack_batch_async, pack_host,
+ unpack_host, pack_host_static) = (getattr(_pycall, n, None) or _late(n) for n in (
+     "pack", "pack_async", "unpack", "unpack_async", "pack_batch", "pack_batch_async", "unpack_batch", "unpack_batch_async",
+     "pack_host", "unpack_host", "pack_host_static"))
 
 
 class Batch:
@@ -277,37 +300,8 @@ class Batch:
         self.ptrs = (ctypes.c_void_p * n)(*[_ptr(b) for b in typed_bufs])
         self.counts = (ctypes.c_int * n)(*counts)
         self.types = (ctypes.c_int32 * n)(*types)
-
-
-def _batch(fn_name, batch, packed, packed_size, position, stream):
-    pos = ctypes.c_int64(position)
-    fn = getattr(lib(), fn_name)
-    if "unpack" in fn_name:
-        rc = fn(batch.n, _ptr(packed), packed_size, ctypes.byref(pos), batch.ptrs, batch.counts, batch.types,
-                _stream(stream))
-    else:
-        rc = fn(batch.n, batch.ptrs, batch.counts, batch.types, _ptr(packed), packed_size, ctypes.byref(pos),
-                _stream(stream))
-    _check(rc, fn_name)
-    return pos.value
-
-
-def pack_batch(batch: Batch, outbuf, outsize: int, position: int, stream=None) -> int:
-    """tp_pack_batch; returns the new position."""
-    return _batch("tp_pack_batch", batch, outbuf, outsize, position, stream)
-
-
-def pack_batch_async(batch: Batch, outbuf, outsize: int, position: int, stream=None) -> int:
-    return _batch("tp_pack_batch_async", batch, outbuf, outsize, position, stream)
-
-
-def unpack_batch(inbuf, insize: int, position: int, batch: Batch, stream=None) -> int:
-    """tp_unpack_batch; returns the new position."""
-    return _batch("tp_unpack_batch", batch, inbuf, insize, position, stream)
-
-
-def unpack_batch_async(inbuf, insize: int, position: int, batch: Batch, stream=None) -> int:
-    return _batch("tp_unpack_batch_async", batch, inbuf, insize, position, stream)
+        # what _pycall reads: the arrays are this object's own and stay where they are
+        self.raw = (n, *(ctypes.addressof(a) for a in (self.ptrs, self.counts, self.types)))
 
 
 # ------------------------------------------------------------------ model and host delivery
@@ -337,37 +331,7 @@ def model_select(t: int, count: int, t_cpu_cpu: float = 0.0, t_gpu_gpu: float = 
     return method.value, list(times)
 
 
-def pack_host(inbuf, incount, t, host_outbuf, outsize, position, staging=None, staging_size=0,
-              method=TP_METHOD_AUTO, stream=None):
-    """tp_pack_host; returns (new position, method used)."""
-    pos, used = ctypes.c_int64(position), ctypes.c_int(-9)
-    rc = lib().tp_pack_host(_ptr(inbuf), incount, t, _ptr(host_outbuf), outsize, ctypes.byref(pos),
-                            _ptr(staging) if staging is not None else None, staging_size, method, _stream(stream),
-                            ctypes.byref(used))
-    _check(rc, "tp_pack_host")
-    return pos.value, used.value
-
-
 TP_STATIC_STAGING_BYTES = 4 << 20
-
-
-def pack_host_static(inbuf, incount, t, host_outbuf, outsize, position, stream=None) -> int:
-    """tp_pack_host_static (staged through the library's fixed device array; allocates nothing); returns the new position."""
-    pos = ctypes.c_int64(position)
-    rc = lib().tp_pack_host_static(_ptr(inbuf), incount, t, _ptr(host_outbuf), outsize, ctypes.byref(pos), _stream(stream))
-    _check(rc, "tp_pack_host_static")
-    return pos.value
-
-
-def unpack_host(host_inbuf, insize, position, outbuf, outcount, t, staging=None, staging_size=0,
-                method=TP_METHOD_AUTO, stream=None):
-    """tp_unpack_host; returns (new position, method used)."""
-    pos, used = ctypes.c_int64(position), ctypes.c_int(-9)
-    rc = lib().tp_unpack_host(_ptr(host_inbuf), insize, ctypes.byref(pos), _ptr(outbuf), outcount, t,
-                              _ptr(staging) if staging is not None else None, staging_size, method, _stream(stream),
-                              ctypes.byref(used))
-    _check(rc, "tp_unpack_host")
-    return pos.value, used.value
 
 
 # ------------------------------------------------------------------ resource cache

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -36,9 +37,22 @@ def build(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    build_pycall()
     for tool in C_TOOLS:
         build_c_tool(tool)
     return LIB_PATH
+
+
+# the extension module that marshals the Python calls (needs no GPU code and no link to the library)
+PYCALL_PATH = os.path.join(PKG_DIR, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def build_pycall() -> str:
+    subprocess.check_call([
+        "gcc", "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+        os.path.join(CSRC, "pycall.c"), "-o", PYCALL_PATH,
+    ])
+    return PYCALL_PATH
 
 
 # plain-C programs that use the library through include/tp_pack.h alone
