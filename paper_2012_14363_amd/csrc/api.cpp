@@ -16,6 +16,7 @@
 #include "kernels.hpp"
 #include "plan.hpp"
 #include "resource_cache.hpp"
+#include "signal.hpp"
 #include "status.hpp"
 #include "transfer.hpp"
 #include "type_tree.hpp"
@@ -203,14 +204,37 @@ int plan_request(bool unpack, const TypeNode& node, const void* typed_buf, int64
     return kSuccess;
 }
 
-int finish(hipStream_t stream, bool synchronize) {
-    if (!synchronize) return kSuccess;
-    const hipError_t e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-        t_last_hip_error = hipGetErrorString(e);
-        return kErrOther;
+// A runtime status as a TP_* one; remembers the message of a failure.
+int outcome(hipError_t e) {
+    if (e == hipSuccess) return kSuccess;
+    (void)hipGetLastError();
+    t_last_hip_error = hipGetErrorString(e);
+    return kErrOther;
+}
+
+// Enqueues the batched, then the single launches of a call, in order, and waits for them if asked to.
+int enqueue_all(const std::vector<BatchParams>& batches, const std::vector<Launch>& singles, bool unpack, hipStream_t stream,
+                bool synchronize) {
+    if (batches.empty() && singles.empty()) return kSuccess;
+    // (the "nt" override asks for other stores than a launch that signals for itself can have)
+    if (synchronize && batches.empty() && singles.size() == 1 && signals_itself(singles[0]) && g_nt.load(std::memory_order_relaxed) < 0) {
+        Signal signal;
+        if (signal.take(singles[0].nblocks)) {
+            const hipError_t e = enqueue_signalled(singles[0], unpack, stream, signal.params());
+            if (e == hipSuccess) return outcome(signal.wait(stream));
+            signal.cancel();
+            return outcome(e);
+        }
     }
-    return kSuccess;
+    for (const BatchParams& b : batches) {
+        const int rc = outcome(enqueue_batch(b, unpack, stream));
+        if (rc != kSuccess) return rc;
+    }
+    for (const Launch& l : singles) {
+        const int rc = outcome(enqueue(l, unpack, stream));
+        if (rc != kSuccess) return rc;
+    }
+    return synchronize ? outcome(hipStreamSynchronize(stream)) : kSuccess;
 }
 
 int transfer(bool unpack, const void* typed_buf, int64_t count, tp_type t, const void* packed_buf,
@@ -232,18 +256,8 @@ int transfer(bool unpack, const void* typed_buf, int64_t count, tp_type t, const
     }
     const int64_t pos = *position + bytes;
     t_last_plan.launches = launches;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    for (const Launch& l : launches) {
-        const hipError_t e = enqueue(l, unpack, stream);
-        if (e != hipSuccess) {
-            t_last_hip_error = hipGetErrorString(e);
-            return kErrOther;
-        }
-    }
-    if (!launches.empty()) {
-        rc = finish(stream, synchronize);
-        if (rc != kSuccess) return rc;
-    }
+    rc = enqueue_all({}, launches, unpack, static_cast<hipStream_t>(hip_stream), synchronize);
+    if (rc != kSuccess) return rc;
     *position = pos;
     return kSuccess;
 }
@@ -280,25 +294,8 @@ int transfer_batch(bool unpack, int n, const void* const* typed_bufs, const int*
     make_batches(launches, &batches, &singles);
     t_last_plan.batches = batches;
     t_last_plan.launches = singles;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    for (const BatchParams& b : batches) {
-        const hipError_t e = enqueue_batch(b, unpack, stream);
-        if (e != hipSuccess) {
-            t_last_hip_error = hipGetErrorString(e);
-            return kErrOther;
-        }
-    }
-    for (const Launch& l : singles) {
-        const hipError_t e = enqueue(l, unpack, stream);
-        if (e != hipSuccess) {
-            t_last_hip_error = hipGetErrorString(e);
-            return kErrOther;
-        }
-    }
-    if (!launches.empty()) {
-        const int rc = finish(stream, synchronize);
-        if (rc != kSuccess) return rc;
-    }
+    const int rc = enqueue_all(batches, singles, unpack, static_cast<hipStream_t>(hip_stream), synchronize);
+    if (rc != kSuccess) return rc;
     *position = pos;
     return kSuccess;
 }
@@ -342,14 +339,7 @@ int copy_device_buffer_to_packed(const void* device_src, int64_t bytes, void* pa
     std::vector<Launch> launches;
     rc = plan_launches(in, &launches);
     if (rc != kSuccess) return rc;
-    for (const Launch& l : launches) {
-        const hipError_t e = enqueue(l, false, stream);
-        if (e != hipSuccess) {
-            t_last_hip_error = hipGetErrorString(e);
-            return kErrOther;
-        }
-    }
-    return kSuccess;
+    return enqueue_all({}, launches, false, stream, false);
 }
 
 }  // namespace tp

@@ -37,7 +37,8 @@ namespace {
 // stores can carry the non-temporal bit (`nt`): the data then does not displace
 // other lines in L2 / Infinity Cache.  NT bit 0: loads, bit 1: stores, bit 2: stores
 // also carry `sc1`, which has L2 write them through at once instead of holding the
-// line until something evicts it.
+// line until something evicts it; bit 3: stores carry `sc0 sc1`, system scope: written
+// through as well, and waiting for the store is waiting until every agent can see it.
 // The word is accessed through a type of alignment 1: the address may be any byte, and
 // the compiler, which knows that this target takes unaligned accesses, still emits one
 // global_load/store of the full width.
@@ -52,7 +53,8 @@ struct DeviceMem {
     template <class W>
     __device__ __forceinline__ void store(char* p, const W& v) const {
         typedef W Unaligned __attribute__((aligned(1)));
-        if constexpr (NT & 4) store_through(p, v);
+        if constexpr (NT & 8) store_visible(p, v);
+        else if constexpr (NT & 4) store_through(p, v);
         else if constexpr (NT & 2) __builtin_nontemporal_store(v, reinterpret_cast<Unaligned*>(p));
         else *reinterpret_cast<Unaligned*>(p) = v;
     }
@@ -78,23 +80,54 @@ struct DeviceMem {
         else
             asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
     }
+    // `global_store ... sc0 sc1 nt`, likewise.
+    template <class W>
+    __device__ __forceinline__ static void store_visible(char* p, const W& v) {
+        if constexpr (sizeof(W) == 1)
+            asm volatile("global_store_byte %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(static_cast<uint32_t>(v)) : "memory");
+        else if constexpr (sizeof(W) == 2)
+            asm volatile("global_store_short %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(static_cast<uint32_t>(v)) : "memory");
+        else if constexpr (sizeof(W) == 4)
+            asm volatile("global_store_dword %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
+        else if constexpr (sizeof(W) == 8)
+            asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
+        else
+            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+    }
 };
 
 template <int WLOG2, int UX, int UR, bool UNPACK, int NRD, int NT>
-__global__ void __launch_bounds__(kBlockThreads) tile_kernel(const KParams p) {
+__global__ void __launch_bounds__(kBlockThreads) tile_kernel(KParams p) {
     // one workgroup per tile, or (staged unpack) fewer workgroups that each take every gridDim.x-th tile
     for (uint32_t tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x)
         tile_thread<WLOG2, UX, UR, UNPACK, NRD>(p, tile, threadIdx.x, DeviceMem<NT>{});
 }
 
+// The end of a workgroup of a launch that signals for itself (signal.hpp).  All its stores were of system
+// scope, so a wave that has waited for them knows they are where every agent sees them; once every wave of the
+// workgroup has, the workgroup counts itself, and the launch's last one tells the host.
+__device__ __forceinline__ void signal_done(const SignalParams& s) {
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    if (s.counter && __hip_atomic_fetch_add(s.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != s.last) return;
+    __hip_atomic_store(s.flag, s.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <int WLOG2, int UX, int UR, bool UNPACK, int NRD>
+__global__ void __launch_bounds__(kBlockThreads) signalled_kernel(KParams p, SignalParams s) {
+    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(p, blockIdx.x, threadIdx.x, DeviceMem<11>{});
+    signal_done(s);
+}
+
 // Read-only pass of a staged unpack: plain (cached) loads, so the bytes stay in this XCD's L2.
-__global__ void __launch_bounds__(kBlockThreads) prefetch_kernel(const PrefetchParams f) {
+__global__ void __launch_bounds__(kBlockThreads) prefetch_kernel(PrefetchParams f) {
     prefetch_thread(f, blockIdx.x, gridDim.x, threadIdx.x, DeviceMem<0>{});
 }
 
 // Transposing tiles through LDS (tile_body.hpp: xpose_phase).
 template <int WLOG2, bool UNPACK, bool SQUARE>
-__global__ void __launch_bounds__(kBlockThreads) xpose_kernel(const XParams p) {
+__global__ void __launch_bounds__(kBlockThreads) xpose_kernel(XParams p) {
     using W = typename WordOf<WLOG2>::type;
     __shared__ W lds[XposeTile<WLOG2>::kLdsWords];
     xpose_phase<WLOG2, UNPACK, true, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<3>{}, lds);
@@ -102,11 +135,17 @@ __global__ void __launch_bounds__(kBlockThreads) xpose_kernel(const XParams p) {
     xpose_phase<WLOG2, UNPACK, false, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<3>{}, lds);
 }
 
+// Puts a kernel of by-value parameters on the stream.
+template <class... P>
+hipError_t launch(void (*fn)(P...), uint32_t grid, hipStream_t stream, const P&... params) {
+    void* args[] = {const_cast<void*>(static_cast<const void*>(&params))...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(grid), dim3(kBlockThreads), args, 0, stream);
+}
+
 template <int WLOG2, bool UNPACK>
-void launch_xpose(const Launch& l, hipStream_t stream) {
-    const dim3 grid(l.nblocks), block(kBlockThreads);
-    if (xpose_is_square(l.x, WLOG2)) hipLaunchKernelGGL((xpose_kernel<WLOG2, UNPACK, true>), grid, block, 0, stream, l.x);
-    else hipLaunchKernelGGL((xpose_kernel<WLOG2, UNPACK, false>), grid, block, 0, stream, l.x);
+hipError_t launch_xpose(const Launch& l, hipStream_t stream) {
+    if (xpose_is_square(l.x, WLOG2)) return launch(xpose_kernel<WLOG2, UNPACK, true>, l.nblocks, stream, l.x);
+    return launch(xpose_kernel<WLOG2, UNPACK, false>, l.nblocks, stream, l.x);
 }
 
 template <bool UNPACK>
@@ -117,14 +156,13 @@ hipError_t enqueue_xpose(const Launch& l, hipStream_t stream) {
         x.pitch < x.te_a * x.ew || uint64_t{x.te_b} * x.pitch > static_cast<uint64_t>(xpose_lds_words(l.word_log2)))
         return hipErrorInvalidValue;
     switch (l.word_log2) {
-    case 0: launch_xpose<0, UNPACK>(l, stream); break;
-    case 1: launch_xpose<1, UNPACK>(l, stream); break;
-    case 2: launch_xpose<2, UNPACK>(l, stream); break;
-    case 3: launch_xpose<3, UNPACK>(l, stream); break;
-    case 4: launch_xpose<4, UNPACK>(l, stream); break;
+    case 0: return launch_xpose<0, UNPACK>(l, stream);
+    case 1: return launch_xpose<1, UNPACK>(l, stream);
+    case 2: return launch_xpose<2, UNPACK>(l, stream);
+    case 3: return launch_xpose<3, UNPACK>(l, stream);
+    case 4: return launch_xpose<4, UNPACK>(l, stream);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // Many planned launches, of different datatypes, as one grid: a workgroup looks up
@@ -132,11 +170,11 @@ hipError_t enqueue_xpose(const Launch& l, hipStream_t stream) {
 // and runs the same tile body.  Saves one launch per datatype where launches are
 // short, e.g. the 26 regions of a halo exchange.
 template <bool UNPACK>
-__global__ void __launch_bounds__(kBlockThreads) batch_kernel(const BatchParams b) {
+__global__ void __launch_bounds__(kBlockThreads) batch_kernel(BatchParams b) {
     batch_thread<UNPACK>(b, blockIdx.x, threadIdx.x, DeviceMem<3>{});
 }
 
-using KernelFn = void (*)(const KParams);
+using KernelFn = void (*)(KParams);
 
 // Visitor for dispatch_launch: the kernel instantiation a launch names.
 template <bool UNPACK>
@@ -157,11 +195,41 @@ struct PickKernel {
     }
 };
 
+template <bool UNPACK>
+struct PickSignalled {
+    void (*fn)(KParams, SignalParams) = nullptr;
+    template <int WLOG2, int UX, int UR, int NRD>
+    void operator()() {
+        fn = signalled_kernel<WLOG2, UX, UR, UNPACK, NRD>;
+    }
+};
+
+constexpr uint32_t kSignalledBlocks = 256;
+
 }  // namespace
+
+bool signals_itself(const Launch& l) {
+    return l.kind == kTile && l.grid == 0 && l.nblocks > 0 && l.nblocks <= kSignalledBlocks;
+}
+
+hipError_t enqueue_signalled(const Launch& l, bool unpack, hipStream_t stream, const SignalParams& signal) {
+    if (!signals_itself(l) || !signal.flag || (l.nblocks > 1) != (signal.counter != nullptr)) return hipErrorInvalidValue;
+    const KParams p = kernel_params(l);
+    void (*fn)(KParams, SignalParams) = nullptr;
+    if (unpack) {
+        PickSignalled<true> pick;
+        if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
+    } else {
+        PickSignalled<false> pick;
+        if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
+    }
+    if (!fn) return hipErrorInvalidValue;
+    return launch(fn, l.nblocks, stream, p, signal);
+}
 
 hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
     if (l.nblocks == 0 || l.grid > l.nblocks || (l.grid ? l.grid : l.nblocks) > kMaxGrid) return hipErrorInvalidValue;
-    const dim3 grid(l.grid ? l.grid : l.nblocks), block(kBlockThreads);
+    const uint32_t grid = l.grid ? l.grid : l.nblocks;
     if (l.kind == kXpose) {
         if (l.grid) return hipErrorInvalidValue;
         return unpack ? enqueue_xpose<true>(l, stream) : enqueue_xpose<false>(l, stream);
@@ -172,8 +240,7 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
         if (!f.base || f.bytes < 16 || f.tile_bytes < 16 || (f.tile_bytes & (f.tile_bytes - 1)) || f.ntiles != l.nblocks ||
             (f.bytes + f.tile_bytes - 1) / f.tile_bytes != f.ntiles)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL(prefetch_kernel, grid, block, 0, stream, f);
-        return hipGetLastError();
+        return launch(prefetch_kernel, grid, stream, f);
     }
     const KParams p = kernel_params(l);
     KernelFn fn = nullptr;
@@ -187,15 +254,12 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
         if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
     }
     if (!fn) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, grid, block, 0, stream, p);
-    return hipGetLastError();
+    return launch(fn, grid, stream, p);
 }
 
 hipError_t enqueue_batch(const BatchParams& b, bool unpack, hipStream_t stream) {
     if (b.n == 0 || b.nblocks == 0 || b.nblocks > kMaxGrid) return hipErrorInvalidValue;
-    if (unpack) hipLaunchKernelGGL(batch_kernel<true>, dim3(b.nblocks), dim3(kBlockThreads), 0, stream, b);
-    else hipLaunchKernelGGL(batch_kernel<false>, dim3(b.nblocks), dim3(kBlockThreads), 0, stream, b);
-    return hipGetLastError();
+    return launch(unpack ? batch_kernel<true> : batch_kernel<false>, b.nblocks, stream, b);
 }
 
 }  // namespace tp
