@@ -43,6 +43,7 @@ std::atomic<int64_t> g_max_words_per_run{int64_t{1} << 30};
 struct LastPlan {
     std::vector<BatchParams> batches;
     std::vector<Launch> launches;
+    std::vector<Launch> scratch;  // of a batched call: one request's launches
     std::string text;
     void clear() {
         batches.clear();
@@ -152,17 +153,24 @@ int data_span(const TypeNode& node, int64_t count, int64_t* lo, int64_t* hi) {
     return kSuccess;
 }
 
-// Checks the buffers of a request that has passed check_request and appends its planned launches
-// to `launches`.  `packed` is the contiguous buffer as the caller passed it.
-int plan_request(bool unpack, const TypeNode& node, const void* typed_buf, int64_t count, const void* packed,
-                 int64_t position, BufferMap* memory, std::vector<Launch>* launches, bool batched = false) {
+// A request whose buffers have been checked: where kernels find them.
+struct Located {
+    const char* typed = nullptr;  // origin of object 0
+    char* packed = nullptr;       // contiguous buffer + position
+    bool packed_on_host = false;
+};
+
+// Checks the buffers of a request that has passed check_request.  `packed` is the contiguous buffer
+// as the caller passed it.
+int locate_request(const TypeNode& node, const void* typed_buf, int64_t count, const void* packed, int64_t position,
+                   BufferMap* memory, Located* out) {
     // Query the first selected byte, not the origin: MPI lets the origin lie outside the
     // allocation (negative strides, lower bounds above zero); the data never does.
     const char* typed = static_cast<const char*>(typed_buf);
     const char* first_byte = nullptr;
     int rc = memory->locate(typed + node.block.start, false, &first_byte);
     if (rc != kSuccess) return rc;
-    const char* typed_view = first_byte - node.block.start;
+    out->typed = first_byte - node.block.start;
     // So are the lowest and the highest byte the request touches, on both sides: a datatype that
     // runs past its buffer is reported here instead of as a GPU memory fault.  (Bytes in between
     // are not queried; an allocation boundary crossed on the way to valid memory goes unnoticed.)
@@ -173,17 +181,15 @@ int plan_request(bool unpack, const TypeNode& node, const void* typed_buf, int64
     if ((rc = memory->check(typed + hi, false)) != kSuccess) return rc;
     const char* packed_first = static_cast<const char*>(packed) + position;
     const char* packed_view = nullptr;
-    bool packed_on_host = false;
-    if ((rc = memory->locate(packed_first, true, &packed_view, &packed_on_host)) != kSuccess) return rc;
-    if ((rc = memory->check(packed_first + count * node.size - 1, true)) != kSuccess) return rc;
+    if ((rc = memory->locate(packed_first, true, &packed_view, &out->packed_on_host)) != kSuccess) return rc;
+    out->packed = const_cast<char*>(packed_view);
+    return memory->check(packed_first + count * node.size - 1, true);
+}
+
+// What the planner needs to know besides the request itself: the direction and the overrides in force.
+PlanInput plan_defaults(bool unpack, bool batched) {
     PlanInput in;
-    in.block = node.block;
-    in.extent = node.extent();
-    in.count = count;
-    in.typed = typed_view;
-    in.packed = const_cast<char*>(packed_view);
     in.unpack = unpack;
-    in.packed_on_host = packed_on_host;
     in.batched = batched;
     in.narrow_partial_rows = g_narrow_partial_rows.load(std::memory_order_relaxed);
     in.max_ur = g_max_ur.load(std::memory_order_relaxed);
@@ -197,11 +203,18 @@ int plan_request(bool unpack, const TypeNode& node, const void* typed_buf, int64
     in.nt = g_nt.load(std::memory_order_relaxed);
     in.max_rows_per_launch = g_max_rows_per_launch.load(std::memory_order_relaxed);
     in.max_words_per_run = g_max_words_per_run.load(std::memory_order_relaxed);
-    std::vector<Launch> mine;
-    rc = plan_launches(in, &mine);
-    if (rc != kSuccess) return rc;
-    launches->insert(launches->end(), mine.begin(), mine.end());
-    return kSuccess;
+    return in;
+}
+
+// Plans a located request into `out` (cleared first).
+int plan_request(const TypeNode& node, int64_t count, const Located& where, PlanInput* in, std::vector<Launch>* out) {
+    in->block = node.block;
+    in->extent = node.extent();
+    in->count = count;
+    in->typed = where.typed;
+    in->packed = where.packed;
+    in->packed_on_host = where.packed_on_host;
+    return plan_launches(*in, out);
 }
 
 // A runtime status as a TP_* one; remembers the message of a failure.
@@ -212,29 +225,29 @@ int outcome(hipError_t e) {
     return kErrOther;
 }
 
-// Enqueues the batched, then the single launches of a call, in order, and waits for them if asked to.
-int enqueue_all(const std::vector<BatchParams>& batches, const std::vector<Launch>& singles, bool unpack, hipStream_t stream,
-                bool synchronize) {
-    if (batches.empty() && singles.empty()) return kSuccess;
+// Enqueues launches in order.
+int enqueue_launches(const std::vector<Launch>& launches, bool unpack, hipStream_t stream) {
+    for (const Launch& l : launches) {
+        const int rc = outcome(enqueue(l, unpack, stream));
+        if (rc != kSuccess) return rc;
+    }
+    return kSuccess;
+}
+
+// The same, and waits for them.
+int run_launches(const std::vector<Launch>& launches, bool unpack, hipStream_t stream) {
     // (the "nt" override asks for other stores than a launch that signals for itself can have)
-    if (synchronize && batches.empty() && singles.size() == 1 && signals_itself(singles[0]) && g_nt.load(std::memory_order_relaxed) < 0) {
+    if (launches.size() == 1 && signals_itself(launches[0]) && g_nt.load(std::memory_order_relaxed) < 0) {
         Signal signal;
-        if (signal.take(singles[0].nblocks)) {
-            const hipError_t e = enqueue_signalled(singles[0], unpack, stream, signal.params());
+        if (signal.take(launches[0].nblocks)) {
+            const hipError_t e = enqueue_signalled(launches[0], unpack, stream, signal.params());
             if (e == hipSuccess) return outcome(signal.wait(stream));
             signal.cancel();
             return outcome(e);
         }
     }
-    for (const BatchParams& b : batches) {
-        const int rc = outcome(enqueue_batch(b, unpack, stream));
-        if (rc != kSuccess) return rc;
-    }
-    for (const Launch& l : singles) {
-        const int rc = outcome(enqueue(l, unpack, stream));
-        if (rc != kSuccess) return rc;
-    }
-    return synchronize ? outcome(hipStreamSynchronize(stream)) : kSuccess;
+    const int rc = enqueue_launches(launches, unpack, stream);
+    return rc == kSuccess ? outcome(hipStreamSynchronize(stream)) : rc;
 }
 
 int transfer(bool unpack, const void* typed_buf, int64_t count, tp_type t, const void* packed_buf,
@@ -243,27 +256,32 @@ int transfer(bool unpack, const void* typed_buf, int64_t count, tp_type t, const
     if (!position) return kErrArg;
     if (*position < 0 || packed_size < 0) return kErrArg;
     t_last_plan.clear();
-    BufferMap memory(buffer_query());
-    if (vouched) memory.add_known(*vouched);
     TypePtr node;
     int64_t bytes = 0;
     int rc = check_request(typed_buf, count, t, packed_buf, packed_size, *position, &node, &bytes);
     if (rc != kSuccess) return rc;
-    std::vector<Launch> launches;
-    if (bytes > 0) {
-        rc = plan_request(unpack, *node, typed_buf, count, packed_buf, *position, &memory, &launches);
-        if (rc != kSuccess) return rc;
-    }
-    const int64_t pos = *position + bytes;
-    t_last_plan.launches = launches;
-    rc = enqueue_all({}, launches, unpack, static_cast<hipStream_t>(hip_stream), synchronize);
+    if (bytes == 0) return kSuccess;
+    BufferMap memory(buffer_query());
+    if (vouched) memory.add_known(*vouched);
+    Located where;
+    rc = locate_request(*node, typed_buf, count, packed_buf, *position, &memory, &where);
     if (rc != kSuccess) return rc;
-    *position = pos;
-    return kSuccess;
+    PlanInput in = plan_defaults(unpack, false);
+    std::vector<Launch>& launches = t_last_plan.launches;   // kept from call to call: planning allocates nothing
+    rc = plan_request(*node, count, where, &in, &launches);
+    if (rc != kSuccess) {
+        launches.clear();
+        return rc;
+    }
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    rc = synchronize ? run_launches(launches, unpack, stream) : enqueue_launches(launches, unpack, stream);
+    if (rc == kSuccess) *position += bytes;
+    return rc;
 }
 
 // n pack (or unpack) requests sharing one contiguous buffer and one running position, enqueued
-// as few launches as possible.  All requests are validated and planned before anything is enqueued.
+// as few launches as possible.  All requests are validated before anything is enqueued; they are then planned
+// and enqueued batch by batch, so that the GPU works on one batch while the next is planned.
 int transfer_batch(bool unpack, int n, const void* const* typed_bufs, const int* counts, const tp_type* types,
                    const void* packed_buf, int64_t packed_size, int64_t* position, void* hip_stream,
                    bool synchronize) {
@@ -271,33 +289,58 @@ int transfer_batch(bool unpack, int n, const void* const* typed_bufs, const int*
     if (n > 0 && (!typed_bufs || !counts || !types)) return kErrArg;
     if (*position < 0 || packed_size < 0) return kErrArg;
     t_last_plan.clear();
-    BufferMap memory(buffer_query());
     int64_t pos = *position;
-    std::vector<TypePtr> nodes(static_cast<size_t>(n));
-    std::vector<int64_t> offsets(static_cast<size_t>(n)), sizes(static_cast<size_t>(n));
+    struct Request {
+        TypePtr node;
+        int64_t offset, size;
+        Located where;
+    };
+    std::vector<Request> requests(static_cast<size_t>(n));
     for (int i = 0; i < n; ++i) {  // every check that needs no device, for all requests, first
-        const int rc = check_request(typed_bufs[i], counts[i], types[i], packed_buf, packed_size, pos, &nodes[i],
-                                     &sizes[i]);
+        Request& r = requests[static_cast<size_t>(i)];
+        const int rc = check_request(typed_bufs[i], counts[i], types[i], packed_buf, packed_size, pos, &r.node, &r.size);
         if (rc != kSuccess) return rc;
-        offsets[i] = pos;
-        pos += sizes[i];
+        r.offset = pos;
+        pos += r.size;
     }
-    std::vector<Launch> launches;
+    BufferMap memory(buffer_query());
     for (int i = 0; i < n; ++i) {
-        if (sizes[i] == 0) continue;
-        const int rc =
-            plan_request(unpack, *nodes[i], typed_bufs[i], counts[i], packed_buf, offsets[i], &memory, &launches, true);
+        Request& r = requests[static_cast<size_t>(i)];
+        if (r.size == 0) continue;
+        const int rc = locate_request(*r.node, typed_bufs[i], counts[i], packed_buf, r.offset, &memory, &r.where);
         if (rc != kSuccess) return rc;
     }
-    std::vector<BatchParams> batches;
-    std::vector<Launch> singles;
-    make_batches(launches, &batches, &singles);
-    t_last_plan.batches = batches;
-    t_last_plan.launches = singles;
-    const int rc = enqueue_all(batches, singles, unpack, static_cast<hipStream_t>(hip_stream), synchronize);
-    if (rc != kSuccess) return rc;
-    *position = pos;
-    return kSuccess;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    PlanInput in = plan_defaults(unpack, true);
+    std::vector<BatchParams>& batches = t_last_plan.batches;
+    std::vector<Launch>& singles = t_last_plan.launches;
+    BatchBuilder group;
+    auto flush = [&]() -> int {
+        if (group.empty()) return kSuccess;
+        batches.emplace_back();
+        group.finish(&batches.back());
+        return outcome(enqueue_batch(batches.back(), unpack, stream));
+    };
+    std::vector<Launch>& mine = t_last_plan.scratch;
+    for (int i = 0; i < n; ++i) {
+        const Request& r = requests[static_cast<size_t>(i)];
+        if (r.size == 0) continue;
+        int rc = plan_request(*r.node, counts[i], r.where, &in, &mine);   // fails on no type that could be committed
+        if (rc != kSuccess) return rc;
+        for (const Launch& l : mine) {
+            if (!batchable(l)) {
+                singles.push_back(l);
+            } else if (!group.add(l)) {
+                if ((rc = flush()) != kSuccess) return rc;
+                group.add(l);
+            }
+        }
+    }
+    int rc = flush();
+    if (rc == kSuccess) rc = enqueue_launches(singles, unpack, stream);
+    if (rc == kSuccess && synchronize && !(batches.empty() && singles.empty())) rc = outcome(hipStreamSynchronize(stream));
+    if (rc == kSuccess) *position = pos;
+    return rc;
 }
 
 }  // namespace
@@ -339,7 +382,7 @@ int copy_device_buffer_to_packed(const void* device_src, int64_t bytes, void* pa
     std::vector<Launch> launches;
     rc = plan_launches(in, &launches);
     if (rc != kSuccess) return rc;
-    return enqueue_all({}, launches, false, stream, false);
+    return enqueue_launches(launches, false, stream);
 }
 
 }  // namespace tp

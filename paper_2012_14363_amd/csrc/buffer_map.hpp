@@ -69,9 +69,10 @@ public:
     size_t known_ranges() const { return known_.size(); }
 
 private:
+    // Newest first: the addresses of one request come one after another, and most lie where the last did.
     const MemRange* find(uintptr_t a) const {
-        for (const MemRange& r : known_)
-            if (r.lo <= a && a < r.hi) return &r;
+        for (size_t i = known_.size(); i-- > 0;)
+            if (known_[i].lo <= a && a < known_[i].hi) return &known_[i];
         return nullptr;
     }
     Query query_;

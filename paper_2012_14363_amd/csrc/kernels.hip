@@ -115,9 +115,19 @@ __device__ __forceinline__ void signal_done(const SignalParams& s) {
 }
 
 template <int WLOG2, int UX, int UR, bool UNPACK, int NRD>
-__global__ void __launch_bounds__(kBlockThreads) signalled_kernel(KParams p, SignalParams s) {
-    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(p, blockIdx.x, threadIdx.x, DeviceMem<11>{});
+__global__ void __launch_bounds__(kBlockThreads) signalled_kernel(BatchDesc d, SignalParams s) {
+    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<11>{});
     signal_done(s);
+}
+
+// The launches that are most of a program's calls: one tile per workgroup, at most three row dimensions.  Their
+// parameters are a BatchDesc, 96 bytes (KParams: 448): above 104 bytes of arguments the runtime's launch was measured to take
+// up to 1.2 us longer on the host (2.6 -> 3.8 us; on other hosts 0.1), which is what bounds calls of up to
+// about 1 MiB.  The grid's size is not read either: it would add 256 bytes of implicit arguments.
+// NRD 0: three row dimensions.
+template <int WLOG2, int UX, int UR, bool UNPACK, int NRD, int NT>
+__global__ void __launch_bounds__(kBlockThreads) tile_kernel(BatchDesc d) {
+    tile_thread<WLOG2, UX, UR, UNPACK, NRD ? NRD : kBatchRowDims>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<NT>{});
 }
 
 // Read-only pass of a staged unpack: plain (cached) loads, so the bytes stay in this XCD's L2.
@@ -195,36 +205,50 @@ struct PickKernel {
     }
 };
 
+// Visitors for the compact launches.
 template <bool UNPACK>
 struct PickSignalled {
-    void (*fn)(KParams, SignalParams) = nullptr;
+    void (*fn)(BatchDesc, SignalParams) = nullptr;
     template <int WLOG2, int UX, int UR, int NRD>
     void operator()() {
-        fn = signalled_kernel<WLOG2, UX, UR, UNPACK, NRD>;
+        fn = signalled_kernel<WLOG2, UX, UR, UNPACK, NRD ? NRD : kBatchRowDims>;
     }
 };
+
+template <bool UNPACK>
+struct PickCompact {
+    int nt = 3;
+    void (*fn)(BatchDesc) = nullptr;
+    template <int WLOG2, int UX, int UR, int NRD>
+    void operator()() {
+        if (nt == 3) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 3>;
+        else if constexpr (UNPACK) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 7>;
+    }
+};
+
+// Whether a launch can have its parameters in a BatchDesc.
+bool fits_compact(const Launch& l) { return l.kind == kTile && l.grid == 0 && l.p.nrd <= static_cast<uint32_t>(kBatchRowDims); }
 
 constexpr uint32_t kSignalledBlocks = 256;
 
 }  // namespace
 
 bool signals_itself(const Launch& l) {
-    return l.kind == kTile && l.grid == 0 && l.nblocks > 0 && l.nblocks <= kSignalledBlocks;
+    return fits_compact(l) && l.nblocks > 0 && l.nblocks <= kSignalledBlocks;
 }
 
 hipError_t enqueue_signalled(const Launch& l, bool unpack, hipStream_t stream, const SignalParams& signal) {
     if (!signals_itself(l) || !signal.flag || (l.nblocks > 1) != (signal.counter != nullptr)) return hipErrorInvalidValue;
-    const KParams p = kernel_params(l);
-    void (*fn)(KParams, SignalParams) = nullptr;
+    void (*fn)(BatchDesc, SignalParams) = nullptr;
     if (unpack) {
         PickSignalled<true> pick;
-        if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
+        if (dispatch_launch(l, l.p.nrd, pick)) fn = pick.fn;
     } else {
         PickSignalled<false> pick;
-        if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
+        if (dispatch_launch(l, l.p.nrd, pick)) fn = pick.fn;
     }
     if (!fn) return hipErrorInvalidValue;
-    return launch(fn, l.nblocks, stream, p, signal);
+    return launch(fn, l.nblocks, stream, compact(l), signal);
 }
 
 hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
@@ -242,15 +266,30 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
             return hipErrorInvalidValue;
         return launch(prefetch_kernel, grid, stream, f);
     }
+    const int nt = l.nt;
+    if (fits_compact(l) && (nt == 3 || (unpack && nt == 7))) {
+        void (*small)(BatchDesc) = nullptr;
+        if (unpack) {
+            PickCompact<true> pick;
+            pick.nt = nt;
+            if (dispatch_launch(l, l.p.nrd, pick)) small = pick.fn;
+        } else {
+            PickCompact<false> pick;
+            pick.nt = nt;
+            if (dispatch_launch(l, l.p.nrd, pick)) small = pick.fn;
+        }
+        if (!small) return hipErrorInvalidValue;
+        return launch(small, grid, stream, compact(l));
+    }
     const KParams p = kernel_params(l);
     KernelFn fn = nullptr;
     if (unpack) {
         PickKernel<true> pick;
-        pick.nt = l.nt;
+        pick.nt = nt;
         if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
     } else {
         PickKernel<false> pick;
-        pick.nt = l.nt;
+        pick.nt = nt;
         if (dispatch_launch(l, p.nrd, pick)) fn = pick.fn;
     }
     if (!fn) return hipErrorInvalidValue;

@@ -1,6 +1,7 @@
 #include "plan.hpp"
 
 #include <algorithm>
+#include <initializer_list>
 #include <limits>
 #include <cstdio>
 
@@ -18,6 +19,7 @@ constexpr int64_t kStagedRows = int64_t{1} << 19;  // fewer rows do not repay th
 // 96 / 128 / 160 / 192 / 224 / 256 / 320 workgroups: 1-byte rows 1766 / 1779 / 1777 / 1750 / 1779 / 1784 / 2097, 2-byte rows
 // 894 / 902 / 892 / 882 / 906 / 971 / -, 8-byte rows 244 / 249 / 243 / 241 / 246 / 259 / -: a flat optimum from 168 to 208.
 constexpr uint32_t kStagedGrid = 192;
+const FastDiv kDivideByOne = make_fastdiv(1);
 constexpr uint32_t kPrefetchGridFactor = 8;        // the read-only pass takes that many times more
 
 struct Dim {
@@ -25,11 +27,28 @@ struct Dim {
     int64_t stride;
 };
 
-int ceil_log2(uint64_t v) {
-    int s = 0;
-    while ((uint64_t{1} << s) < v) ++s;
-    return s;
-}
+// The dimensions of a request, innermost first: a StridedBlock's and the object count.  Planning runs on every
+// call, so it works in place: no allocations, and launches are filled in where they are kept.
+class Dims {
+public:
+    Dims() = default;
+    Dims(std::initializer_list<Dim> init) {
+        for (const Dim& d : init) push_back(d);
+    }
+    void push_back(const Dim& d) { d_[n_++] = d; }
+    void pop_back() { --n_; }
+    size_t size() const { return n_; }
+    Dim& operator[](size_t i) { return d_[i]; }
+    const Dim& operator[](size_t i) const { return d_[i]; }
+    Dim& back() { return d_[n_ - 1]; }
+    const Dim& back() const { return d_[n_ - 1]; }
+
+private:
+    size_t n_ = 0;
+    Dim d_[kMaxDims + 1];
+};
+
+int ceil_log2(uint64_t v) { return v <= 1 ? 0 : 64 - __builtin_clzll(v - 1); }
 
 // Thread-tile shape for runs of n0 words (Sec. 3.3 maps X to the run and fills the
 // block with further rows; here the block is flat and the split is a power of two).
@@ -37,25 +56,37 @@ int ceil_log2(uint64_t v) {
 // that pads the run least wins (1025 words: five chunks of 256 rather than two of 1024), the
 // larger on a tie since its row arithmetic is scalar.
 // `ur_short`: rows per thread (1 or 4) where a run fits the workgroup.
-void choose_tile(uint32_t n0, int ur_short, Launch* l) {
-    if (n0 <= static_cast<uint32_t>(kBlockThreads)) {
-        l->p.bx_log2 = static_cast<uint32_t>(ceil_log2(n0));
-        l->ux = 1;
-        l->ur = ur_short;
-        return;
-    }
-    l->p.bx_log2 = 8;
+struct TileShape {
+    uint32_t bx_log2;
+    int ux, ur;
+};
+
+TileShape choose_tile(uint32_t n0, int ur_short) {
+    if (n0 <= static_cast<uint32_t>(kBlockThreads)) return {static_cast<uint32_t>(ceil_log2(n0)), 1, ur_short};
+    TileShape t{8, 1, 4};
     uint64_t best = ~uint64_t{0};
     for (int ux : {4, 2, 1}) {
-        const uint64_t chunk = static_cast<uint64_t>(kBlockThreads) * ux;
-        const uint64_t padded = (n0 + chunk - 1) / chunk * chunk;
+        const uint64_t chunk = static_cast<uint64_t>(kBlockThreads) * ux;   // a power of two
+        const uint64_t padded = (n0 + chunk - 1) & ~(chunk - 1);
         if (padded < best) {
             best = padded;
-            l->ux = ux;
+            t.ux = ux;
         }
     }
-    l->ur = 4 / l->ux;
+    t.ur = 4 / t.ux;
+    return t;
 }
+
+// Chunks along a run of n0 words, and row chunks over `rows` (the tile's edges are powers of two).
+uint64_t chunks_along(const TileShape& t, uint64_t n0) {
+    const uint32_t log2 = t.bx_log2 + static_cast<uint32_t>(t.ux >> 1);   // ux 1, 2, 4
+    return (n0 + (uint64_t{1} << log2) - 1) >> log2;
+}
+uint64_t row_chunks(const TileShape& t, uint64_t rows) {
+    const uint32_t log2 = 8 - t.bx_log2 + static_cast<uint32_t>(t.ur >> 1);
+    return (rows + (uint64_t{1} << log2) - 1) >> log2;
+}
+static_assert(kBlockThreads == 1 << 8, "row_chunks");
 
 struct Splitter {
     const PlanInput& in;
@@ -72,8 +103,9 @@ struct Splitter {
     uint32_t words(int64_t bytes) const { return static_cast<uint32_t>((bytes + word() - 1) >> word_log2); }
 
     // One launch over dims[0..nd): dims[0].count bytes per run.
-    void add(const std::vector<Dim>& dims, const char* typed, char* packed) {
-        Launch l;
+    void add(const Dims& dims, const char* typed, char* packed) {
+        out->emplace_back();
+        Launch& l = out->back();
         l.word_log2 = word_log2;
         KParams& p = l.p;
         p.strided = typed;
@@ -92,36 +124,36 @@ struct Splitter {
             rows *= static_cast<uint64_t>(dims[d].count);
         }
         p.nrows = static_cast<uint32_t>(rows);
-        choose_tile(p.n0, ur_short, &l);
+        const TileShape t = choose_tile(p.n0, ur_short);
+        p.bx_log2 = t.bx_log2;
+        l.ux = t.ux;
+        l.ur = t.ur;
         l.nt = nt;
-        const uint32_t bx = 1u << p.bx_log2;
-        const uint32_t br = kBlockThreads >> p.bx_log2;
-        p.nxc = (p.n0 + bx * l.ux - 1) / (bx * l.ux);
+        p.nxc = static_cast<uint32_t>(chunks_along(t, p.n0));
         p.xc_div = make_fastdiv(p.nxc);
-        const uint64_t nrc = (rows + uint64_t{br} * l.ur - 1) / (uint64_t{br} * l.ur);
-        l.nblocks = static_cast<uint32_t>(nrc * p.nxc);
+        l.nblocks = static_cast<uint32_t>(row_chunks(t, rows) * p.nxc);
         if (grid) l.grid = std::min(grid, l.nblocks);
         else if (l.nblocks > kMaxGrid) l.grid = kMaxGrid;   // more tiles than a grid may have workgroups
-        out->push_back(l);
     }
 
     // Largest row count for which block ids stay below 2^30 with runs of n0 words.
     int64_t row_limit(int64_t n0) const {
-        Launch probe;
-        choose_tile(static_cast<uint32_t>(n0), ur_short, &probe);
-        const int64_t bx = int64_t{1} << probe.p.bx_log2;
-        const int64_t br = kBlockThreads >> probe.p.bx_log2;
-        const int64_t nxc = (n0 + bx * probe.ux - 1) / (bx * probe.ux);
-        const int64_t by_blocks = ((int64_t{1} << 30) / nxc) * br * probe.ur;
+        const TileShape t = choose_tile(static_cast<uint32_t>(n0), ur_short);
+        const int64_t nxc = static_cast<int64_t>(chunks_along(t, static_cast<uint64_t>(n0)));
+        const int64_t by_blocks = ((int64_t{1} << 30) / nxc) * (kBlockThreads >> t.bx_log2) * t.ur;
         const int64_t limit = std::min(in.max_rows_per_launch, by_blocks);
         return std::max<int64_t>(1, chunk_rows > 0 ? std::min(limit, chunk_rows) : limit);
     }
 
     // Rows: split the outermost dimension until a launch's row count fits.
-    void split_rows(std::vector<Dim> dims, const char* typed, char* packed) {
+    void split_rows(const Dims& dims, const char* typed, char* packed) {
         int64_t rows = 1;
         for (size_t d = 1; d < dims.size(); ++d) rows *= dims[d].count;
-        const int64_t limit = row_limit(words(dims[0].count));
+        const uint32_t n0 = words(dims[0].count);
+        // (the first comparison spares nearly every call the limit's division)
+        const bool few = rows <= (int64_t{1} << 20) && n0 <= static_cast<uint32_t>(kBlockThreads) && rows <= in.max_rows_per_launch &&
+                         chunk_rows == 0;
+        const int64_t limit = few ? rows : row_limit(n0);
         if (rows <= limit) {
             add(dims, typed, packed);
             return;
@@ -131,7 +163,7 @@ struct Splitter {
         const int64_t chunk = std::max<int64_t>(1, limit / inner_rows);
         for (int64_t i = 0; i < top.count; i += chunk) {
             const int64_t k = std::min(chunk, top.count - i);
-            std::vector<Dim> sub = dims;
+            Dims sub = dims;
             if (inner_rows > limit) sub.pop_back(); else sub.back().count = k;
             split_rows(sub, typed + i * top.stride, packed + i * inner_rows * row_pitch);
         }
@@ -140,7 +172,7 @@ struct Splitter {
     // Runs longer than the per-launch word limit are cut into pieces along dimension 0.  A piece
     // is a run of its own and needs at least one word, so a last piece shorter than that starts
     // early instead and overlaps the piece before it (same bytes written twice).
-    void split_runs(const std::vector<Dim>& dims, const char* typed, char* packed) {
+    void split_runs(const Dims& dims, const char* typed, char* packed) {
         const int64_t piece = in.max_words_per_run << word_log2;
         const int64_t total = dims[0].count;
         for (int64_t off = 0; off < total; off += piece) {
@@ -149,7 +181,11 @@ struct Splitter {
                 at = total - word();
                 len = word();
             }
-            std::vector<Dim> sub = dims;
+            if (len == total) {
+                split_rows(dims, typed, packed);
+                return;
+            }
+            Dims sub = dims;
             sub[0].count = len;
             split_rows(sub, typed + at, packed + at);
         }
@@ -160,7 +196,7 @@ struct Splitter {
 // words of the widest power of two dividing their length) and some outer row dimension A steps
 // by exactly one element while the innermost row dimension B strides over at least two.  Returns false (and leaves `out` alone) when it does not apply or the launch would not
 // fit one grid.
-bool plan_xpose(const PlanInput& in, const std::vector<Dim>& dims, const char* typed, std::vector<Launch>* out) {
+bool plan_xpose(const PlanInput& in, const Dims& dims, const char* typed, std::vector<Launch>* out) {
     if (!in.allow_xpose || dims.size() < 3) return false;
     const int64_t run = dims[0].count;
     if (run > 64) return false;
@@ -275,8 +311,8 @@ bool plan_xpose(const PlanInput& in, const std::vector<Dim>& dims, const char* t
 // read-only pass that brings its packed bytes into L2 followed by the store passes, all with the
 // same few workgroups taking the same tiles: workgroup ids map to XCDs round-robin, so a tile's
 // bytes wait in the L2 its stores will ask.  Returns false where this does not apply.
-bool plan_staged(const PlanInput& in, const std::vector<Dim>& all_dims, const char* typed, std::vector<Launch>* out) {
-    std::vector<Dim> dims = {all_dims[0]};
+bool plan_staged(const PlanInput& in, const Dims& all_dims, const char* typed, std::vector<Launch>* out) {
+    Dims dims = {all_dims[0]};
     for (size_t d = 1; d < all_dims.size(); ++d)
         if (all_dims[d].count != 1) dims.push_back(all_dims[d]);   // a dimension of one row is none
     if (dims.size() < 2) return false;
@@ -335,7 +371,7 @@ bool plan_staged(const PlanInput& in, const std::vector<Dim>& all_dims, const ch
         for (int64_t p = 0; p < passes && p < n; ++p) {
             // rows lo + p, lo + p + passes, ...: `passes` rows apart on both sides
             Splitter s{in, word_log2, run * passes, out, 1, in.nt >= 0 ? in.nt : 6, grid};
-            const std::vector<Dim> sub = {{run, 1}, {(n - p + passes - 1) / passes, pitch * passes}};
+            const Dims sub = {{run, 1}, {(n - p + passes - 1) / passes, pitch * passes}};
             s.add(sub, typed + (lo + p) * pitch, in.packed + (lo + p) * run);
         }
     }
@@ -349,7 +385,7 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
     const StridedBlock& sb = in.block;
     if (in.count == 0 || sb.counts[0] == 0) return kSuccess;
 
-    std::vector<Dim> dims;
+    Dims dims;
     for (int d = 0; d < sb.ndims; ++d) dims.push_back({sb.counts[d], sb.strides[d]});
     // The object count is one more outer dimension of stride `extent` (Sec. 3.3 handles it
     // with the grid's Z dimension); fold or flatten it away when objects abut.
@@ -444,9 +480,7 @@ bool batchable(const Launch& l) {
            (l.nt & 4) == 0 && l.grid == 0;
 }
 
-namespace {
-
-BatchDesc make_desc(const Launch& l) {
+BatchDesc compact(const Launch& l) {
     BatchDesc d;
     const KParams& p = l.p;
     d.strided = p.strided;
@@ -456,55 +490,66 @@ BatchDesc make_desc(const Launch& l) {
     d.nrows = p.nrows;
     d.nxc = p.nxc;
     d.xc_mul = p.xc_div.mul;
-    d.xc_shift = static_cast<uint8_t>(p.xc_div.shift);
-    d.bx_log2 = static_cast<uint8_t>(p.bx_log2);
-    d.word_log2 = static_cast<uint8_t>(l.word_log2);
-    d.tile = static_cast<uint8_t>((l.ux == 1 ? 0 : l.ux == 2 ? 1 : 2) | (p.tail_back << 4));
-    d.nrd = static_cast<uint8_t>(p.nrd == 0 ? 1 : p.nrd);
-    const FastDiv one = make_fastdiv(1);
+    const uint32_t tile = (l.ux == 1 ? 0u : l.ux == 2 ? 1u : 2u) | (p.tail_back << 4);
+    d.shape = p.bx_log2 | static_cast<uint32_t>(l.word_log2) << 8 | tile << 16 | (p.nrd == 0 ? 1u : p.nrd) << 24;
+    d.shifts = p.xc_div.shift << 24;
     for (int k = 0; k < kBatchRowDims; ++k) {
         const bool used = static_cast<uint32_t>(k) < p.nrd;
         d.rstride[k] = used ? p.rstride[k] : 0;
         d.rcount[k] = used ? p.rcount[k] : 1;
-        d.rmul[k] = used ? p.rdiv[k].mul : one.mul;
-        d.rshift[k] = static_cast<uint8_t>(used ? p.rdiv[k].shift : one.shift);
+        d.rmul[k] = used ? p.rdiv[k].mul : kDivideByOne.mul;
+        d.shifts |= (used ? p.rdiv[k].shift : kDivideByOne.shift) << (8 * k);
     }
     return d;
 }
 
-}  // namespace
+bool BatchBuilder::add(const Launch& l) {
+    // one tile per workgroup: a batch has at most as many tiles as a grid may have workgroups
+    const bool fits = n_ < static_cast<uint32_t>(kBatchMax) && total_ + l.nblocks <= kMaxGrid;
+    if (!fits) return false;
+    desc_[n_] = compact(l);
+    nblocks_[n_] = l.nblocks;
+    total_ += l.nblocks;
+    ++n_;
+    return true;
+}
+
+void BatchBuilder::finish(BatchParams* out) {
+    // Largest first: workgroups are handed out in index order, so the big descriptors start
+    // while the whole chip is free and the small ones fill in behind them.  Each descriptor
+    // carries its own addresses, so the order inside a launch is free.
+    uint8_t order[kBatchMax];
+    for (uint32_t i = 0; i < n_; ++i) {
+        uint32_t at = i;
+        for (; at > 0 && nblocks_[order[at - 1]] < nblocks_[i]; --at) order[at] = order[at - 1];
+        order[at] = static_cast<uint8_t>(i);
+    }
+    out->n = n_;
+    out->nblocks = 0;
+    for (uint32_t i = 0; i < n_; ++i) {
+        out->d[i] = desc_[order[i]];
+        out->nblocks += nblocks_[order[i]];
+        out->block_end[i] = out->nblocks;
+    }
+    n_ = 0;
+    total_ = 0;
+}
 
 void make_batches(const std::vector<Launch>& launches, std::vector<BatchParams>* batches,
                   std::vector<Launch>* singles) {
-    std::vector<const Launch*> group;
-    uint64_t group_blocks = 0;
+    BatchBuilder group;
     auto flush = [&] {
         if (group.empty()) return;
-        // Largest first: workgroups are handed out in index order, so the big descriptors start
-        // while the whole chip is free and the small ones fill in behind them.  Each descriptor
-        // carries its own addresses, so the order inside a launch is free.
-        std::stable_sort(group.begin(), group.end(),
-                         [](const Launch* a, const Launch* b) { return a->nblocks > b->nblocks; });
-        BatchParams cur;
-        for (const Launch* l : group) {
-            cur.d[cur.n] = make_desc(*l);
-            cur.nblocks += l->nblocks;
-            cur.block_end[cur.n] = cur.nblocks;
-            ++cur.n;
-        }
-        batches->push_back(cur);
-        group.clear();
-        group_blocks = 0;
+        batches->emplace_back();
+        group.finish(&batches->back());
     };
     for (const Launch& l : launches) {
         if (!batchable(l)) {
             singles->push_back(l);
-            continue;
+        } else if (!group.add(l)) {
+            flush();
+            group.add(l);
         }
-        // one tile per workgroup: a batch has at most as many tiles as a grid may have workgroups
-        if (group.size() == static_cast<size_t>(kBatchMax) || group_blocks + l.nblocks > kMaxGrid) flush();
-        group.push_back(&l);
-        group_blocks += l.nblocks;
     }
     flush();
 }

@@ -150,23 +150,46 @@ struct BatchDesc {
     uint32_t rcount[kBatchRowDims];
     uint32_t rmul[kBatchRowDims];
     uint32_t n0, nrows, nxc, xc_mul;
-    uint8_t rshift[kBatchRowDims];
-    uint8_t xc_shift, bx_log2, word_log2;
-    uint8_t tile;  // bits 0-1: 0 = (ux,ur) (1,4), 1 = (2,2), 2 = (4,1); bits 4-7: tail_back
-    uint8_t nrd;   // 1..kBatchRowDims
+    // Small fields in whole words: the scalar unit loads nothing smaller, and a byte field read by a vector load puts a
+    // memory round trip in front of every workgroup.
+    uint32_t shifts;  // of the divisions: row dimension k's in byte k, the x-chunks' in byte 3
+    uint32_t shape;   // byte 0: bx_log2; 1: word_log2; 2: tile: bits 0-1: 0 = (ux,ur) (1,4), 1 = (2,2), 2 = (4,1), bits
+                      // 4-7: tail_back; 3: nrd, 1..kBatchRowDims
+    TP_HD uint32_t bx_log2() const { return shape & 0xffu; }
+    TP_HD uint32_t word_log2() const { return (shape >> 8) & 0xffu; }
+    TP_HD uint32_t tile() const { return (shape >> 16) & 3u; }
+    TP_HD uint32_t tail_back() const { return (shape >> 20) & 15u; }
+    TP_HD uint32_t nrd() const { return shape >> 24; }
 };
 static_assert(sizeof(BatchDesc) == 96, "BatchDesc must stay 96 bytes");
 
 struct BatchParams {
     uint32_t n = 0;                    // descriptors in use
     uint32_t nblocks = 0;              // == block_end[n - 1]
-    uint32_t block_end[kBatchMax] = {};  // descriptor j owns workgroups [block_end[j-1], block_end[j])
+    uint32_t block_end[kBatchMax];     // descriptor j owns workgroups [block_end[j-1], block_end[j])
     BatchDesc d[kBatchMax];
 };
 static_assert(sizeof(BatchParams) <= 4096, "BatchParams must fit the kernel-argument segment");
 
 // True if a launch can ride in a batch (few enough row dimensions).
 bool batchable(const Launch& l);
+// A row-by-row launch of at most kBatchRowDims row dimensions as such a descriptor.
+BatchDesc compact(const Launch& l);
+
+// Collects the descriptors of one batched launch.
+class BatchBuilder {
+public:
+    bool empty() const { return n_ == 0; }
+    bool add(const Launch& l);         // false: the batch is full, finish it first (an empty one takes any launch)
+    void finish(BatchParams* out);     // writes the batch and starts the next
+
+private:
+    uint32_t n_ = 0;
+    uint64_t total_ = 0;
+    uint32_t nblocks_[kBatchMax];
+    BatchDesc desc_[kBatchMax];
+};
+
 // Groups launches into batches of at most kBatchMax descriptors, in order.  Launches that are
 // not batchable are appended to `singles`.
 void make_batches(const std::vector<Launch>& launches, std::vector<BatchParams>* batches,

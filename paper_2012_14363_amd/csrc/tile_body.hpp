@@ -292,16 +292,16 @@ TP_HD inline SmallParams unpack_desc(const BatchDesc& d) {
     p.row_pitch = d.row_pitch;
     p.n0 = d.n0;
     p.nrows = d.nrows;
-    p.bx_log2 = d.bx_log2;
+    p.bx_log2 = d.bx_log2();
     p.nxc = d.nxc;
-    p.nrd = d.nrd;
-    p.tail_back = d.tile >> 4;
+    p.nrd = d.nrd();
+    p.tail_back = d.tail_back();
     p.xc_div.mul = d.xc_mul;
-    p.xc_div.shift = d.xc_shift;
+    p.xc_div.shift = d.shifts >> 24;
     p.xc_div.divisor = d.nxc;
     for (int k = 0; k < kBatchRowDims; ++k) {
         p.rdiv[k].mul = d.rmul[k];
-        p.rdiv[k].shift = d.rshift[k];
+        p.rdiv[k].shift = (d.shifts >> (8 * k)) & 0xffu;
         p.rdiv[k].divisor = d.rcount[k];
         p.rcount[k] = d.rcount[k];
         p.rstride[k] = d.rstride[k];
@@ -327,7 +327,7 @@ TP_HD inline void batch_thread(const BatchParams& b, uint32_t block, uint32_t ti
     const uint32_t first = j == 0 ? 0u : b.block_end[j - 1];
     const SmallParams p = unpack_desc(b.d[j]);
     const uint32_t local = block - first;
-    const uint32_t wl = b.d[j].word_log2, tile = b.d[j].tile & 3u, nrd = b.d[j].nrd;
+    const uint32_t wl = b.d[j].word_log2(), tile = b.d[j].tile(), nrd = b.d[j].nrd();
 #define TP_BATCH_CASE(WL, X, R, N) tile_thread<WL, X, R, UNPACK, N>(p, local, tid, mem)
 #define TP_BATCH_NRD(WL, X, R)            \
     do {                                  \
