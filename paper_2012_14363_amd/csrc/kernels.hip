@@ -116,7 +116,7 @@ __device__ __forceinline__ void signal_done(const SignalParams& s) {
 
 template <int WLOG2, int UX, int UR, bool UNPACK, int NRD>
 __global__ void __launch_bounds__(kBlockThreads) signalled_kernel(BatchDesc d, SignalParams s) {
-    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<11>{});
+    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<10>{});
     signal_done(s);
 }
 
@@ -221,8 +221,12 @@ struct PickCompact {
     void (*fn)(BatchDesc) = nullptr;
     template <int WLOG2, int UX, int UR, int NRD>
     void operator()() {
-        if (nt == 3) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 3>;
-        else if constexpr (UNPACK) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 7>;
+        if (nt == 2) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 2>;
+        else if (nt == 3) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 3>;
+        if constexpr (UNPACK && UX == 1 && UR == 1) {   // written through: planned with one word per thread alone
+            if (nt == 6) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 6>;
+            else if (nt == 7) fn = tile_kernel<WLOG2, UX, UR, UNPACK, NRD, 7>;
+        }
     }
 };
 
@@ -266,8 +270,8 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
             return hipErrorInvalidValue;
         return launch(prefetch_kernel, grid, stream, f);
     }
-    const int nt = l.nt;
-    if (fits_compact(l) && (nt == 3 || (unpack && nt == 7))) {
+    const int nt = l.hints();
+    if (fits_compact(l) && (nt == 2 || nt == 3 || (unpack && nt >= 6 && l.ux == 1 && l.ur == 1))) {
         void (*small)(BatchDesc) = nullptr;
         if (unpack) {
             PickCompact<true> pick;

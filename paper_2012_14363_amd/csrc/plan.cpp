@@ -14,6 +14,9 @@ namespace {
 constexpr int64_t kPageBytes = 4096;  // rows at least this far apart each need their own address translation
 constexpr int64_t kLineBytes = 128;   // memory line: what a partial write is read-modify-written in
 constexpr int64_t kSoloRows = int64_t{1} << 20, kSoloBytes = int64_t{8} << 20;  // batch requests worth their own launch
+constexpr int64_t kManyRows = 128, kManyBytes = int64_t{1} << 20;   // requests whose memory traffic, not latency, decides
+constexpr int64_t kFillBytes = int64_t{4} << 20;  // more than 1024 workgroups of one 16-byte word per thread: four for each CU
+constexpr int64_t kKeepBytes = int64_t{64} << 20; // a quarter of the Infinity Cache
 constexpr int64_t kStagedRows = int64_t{1} << 19;  // fewer rows do not repay the extra passes (2^18: 15.0 against 14.5 us; 2^19: 22 against 26)
 // Workgroups of a staged launch: a multiple of the eight XCDs.  Measured on 64 MiB of rows at 512-byte pitch, us for
 // 96 / 128 / 160 / 192 / 224 / 256 / 320 workgroups: 1-byte rows 1766 / 1779 / 1777 / 1750 / 1779 / 1784 / 2097, 2-byte rows
@@ -73,7 +76,10 @@ TileShape choose_tile(uint32_t n0, int ur_short) {
             t.ux = ux;
         }
     }
-    t.ur = 4 / t.ux;
+    // One row per thread asked for: one word too, unless chunks of 256 would leave a quarter of their lanes idle and
+    // wider ones no more of them (313 words: 25 us in single words, 21 in tiles of two words by two rows).
+    if (ur_short == 1 && (t.ux == 1 || n0 * 4 >= best * 3)) t.ux = t.ur = 1;
+    else t.ur = 4 / t.ux;
     return t;
 }
 
@@ -419,15 +425,20 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
     // one another in the packed stream (the innermost row dimension), and how close do rows come
     // that are written far apart in time (the outer row dimensions)?
     bool partial_rows = false;
+    uint64_t bits = static_cast<uint64_t>(run) | reinterpret_cast<uintptr_t>(typed);
     int64_t inner_pitch = 0, outer_pitch = std::numeric_limits<int64_t>::max();
+    // Does a dimension step back into what the ones inside it have walked over (interleaved or overlapping rows)?
+    bool revisits = false;
+    int64_t reach = run;
     if (dims.size() > 1) {
-        uint64_t bits = static_cast<uint64_t>(run) | reinterpret_cast<uintptr_t>(typed);
         for (size_t d = 1; d < dims.size(); ++d) {
             const int64_t step = dims[d].stride < 0 ? -dims[d].stride : dims[d].stride;
             bits |= static_cast<uint64_t>(step);
             if (dims[d].count == 1) continue;
             if (inner_pitch == 0) inner_pitch = step;
             else outer_pitch = std::min(outer_pitch, step);
+            if (step < reach) revisits = true;
+            reach = std::max(reach, step * dims[d].count);
         }
         partial_rows = (bits & static_cast<uint64_t>(kLineBytes - 1)) != 0;
     }
@@ -435,19 +446,41 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
     // for a launch of its own to pay (a launch costs about 5 us on the stream).
     int64_t rows = 1;
     for (size_t d = 1; d < dims.size(); ++d) rows *= dims[d].count;
-    const bool own_launch = !in.batched || rows >= kSoloRows || rows * run >= kSoloBytes;
-    if (in.unpack && !in.packed_on_host && in.unpack_rule == 1 && in.narrow_partial_rows && partial_rows &&
-        inner_pitch < kPageBytes && outer_pitch >= kLineBytes && own_launch) {
-        if (in.stage != 0 && plan_staged(in, dims, typed, out)) return kSuccess;
-        // Rows that end in partially written memory lines, follow one another closer than a page and
-        // share no line with rows of another outer index (those L2 should keep and merge): their
-        // stores are written through L2 at once (`sc1 nt`) rather than left for eviction, a thread
-        // takes one row, not four, and a row is spread over 8 to 15 lanes.  Measured on 32 MiB of rows
-        // from rotating sources, against four rows per thread and plain streaming stores in 4-byte
-        // words, us: 512-byte pitch: 12-byte rows 130 -> 112, 48: 39 -> 32, 100: 31 -> 23, 200: 20.4 ->
-        // 18.7; 128-byte pitch: 16-byte rows 95 -> 57; 64-byte rows (half lines) at 256: 36 -> 29.  Rows
-        // a page or more apart lose a few per cent this way (each row its own address translation,
-        // which four rows per thread hide better), whole-line rows gain nothing.
+    const int64_t bytes = rows * run;
+    const bool own_launch = !in.batched || rows >= kSoloRows || bytes >= kSoloBytes;
+    const bool tuned = !in.batched && !in.packed_on_host && in.unpack_rule == 1;
+    const bool through = in.unpack && !in.packed_on_host && in.unpack_rule == 1 && in.narrow_partial_rows && partial_rows &&
+                         inner_pitch < kPageBytes && outer_pitch >= kLineBytes && own_launch;
+    if (through && in.stage != 0 && plan_staged(in, dims, typed, out)) return kSuccess;
+    if (in.unpack && tuned && in.narrow_partial_rows && partial_rows && outer_pitch >= kLineBytes && rows >= kManyRows &&
+        bytes >= kManyBytes) {
+        // Many rows that end in partially written memory lines.  Measured on 24 and 64 MiB of rows of 1 to 65536
+        // bytes at pitches from 5 % above the run to 12 KiB, sources from HBM and from the Infinity Cache, with
+        // every word, one and four rows per thread, and streaming (`nt`) or written-through (`sc1 nt`) stores.
+        //   Stores: written through L2 at once where a line holds at most two rows and rows are short (128-byte
+        // pitch, 64 MiB: 12-byte rows 139 us against 195 streaming, 24: 72 / 100, 48: 41 / 53; 1-KiB pitch,
+        // 256-byte rows 39.6 / 42.6).  Streaming where neighbouring rows share their lines, so that L2 can merge
+        // them (12-byte rows at 13: 46 / 132, 24 at 25: 40 / 71, 64 at 67: 35 / 38), and for rows beyond 1 KiB
+        // (2408 bytes at 4096: 24.8 / 27.3).
+        //   Word: 17 to 32 lanes on a row of at least 128 bytes, 9 to 16 on a shorter one, and no less than 4 bytes
+        // (128-byte rows at 512, words of 4 / 8 / 16: 45 / 54 / 62; 256-byte rows 46 / 31 / 38; 24-byte rows at 64, 2 / 4: 110 / 70).
+        //   One row per thread, except where rows are so close (or, short ones, so far apart: one address
+        // translation each) that four are the better (24 at 25: 40 / 47; 24 at 4096: 13.1 / 16.5).
+        const bool shared_lines = inner_pitch < kLineBytes / 2 || (inner_pitch < kLineBytes * 3 / 2 && inner_pitch - run < 32);
+        //   Rows of whole aligned 64-byte blocks: 8 lanes (64 bytes at 512, words of 4 / 8 / 16: 43.6 / 30.3 / 32.7).
+        const bool blocks = (bits & 63) == 0;
+        const int64_t lanes = blocks ? 8 : run >= kLineBytes ? 32 : inner_pitch < kLineBytes * 3 / 2 && run > 32 ? 8 : 16;
+        // (exceptions: short rows 512 to 1023 bytes apart, 24 at 512, words of 2 / 4: 69 / 83; 12 at 384, 1 / 4: 41.1 / 43.8)
+        const bool narrow = (run <= 32 && inner_pitch >= 512 && inner_pitch < 1024) || (run < 16 && inner_pitch >= 2 * kLineBytes);
+        const int by_lanes = run < 4 ? 0 : narrow ? (run >= 16 ? 1 : 0) : std::max(2, ceil_log2(static_cast<uint64_t>((run + lanes - 1) / lanes)));
+        word_log2 = std::min(word_log2, by_lanes);
+        ur_short = (run <= 32 && inner_pitch < kLineBytes / 2) || (run < 64 && inner_pitch >= kPageBytes) ? 4 : 1;
+        nt = ur_short == 1 && !shared_lines && run <= 1024 ? 7 : 3;
+    } else if (through) {
+        // Fewer rows than that, closer than a page, that share no line with rows of another outer index: written through
+        // L2 at once as well, one row per thread, a row spread over 8 to 15 lanes (32 MiB of rows at 512-byte pitch,
+        // against four rows per thread and streaming stores in 4-byte words, us: 12-byte rows 130 -> 112, 48: 39 -> 32,
+        // 100: 31 -> 23, 200: 20.4 -> 18.7).
         nt = 7;
         ur_short = 1;
         const int eighth_log2 = run >= 16 ? 63 - __builtin_clzll(static_cast<uint64_t>(run / 8)) : 0;
@@ -466,11 +499,39 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
             const int quarter_log2 = run >= 4 ? 63 - __builtin_clzll(static_cast<uint64_t>(run / 4)) : 0;
             word_log2 = std::min(word_log2, std::min(2, quarter_log2));
         }
+        // One word per thread, and so more and shorter workgroups, once there are enough of them to fill the
+        // chip several times over: for long runs (64 MiB, us, against four words per thread: dense 24.2 -> 23.7, 1000 bytes at
+        // 1024: 25.1 -> 23.8, 2408 at 4096: 28.3 -> 24.3, 9000 at 12288: 27.2 -> 24.5), and when packing from
+        // rows far apart (100 at 512: 27.9 -> 26.3), short ones where their distance is a multiple of 512 bytes (12 at 512: 46 ->
+        // 42, 32 at 512: 52 -> 47; but 20 at 1000: 30.3 -> 31.5); short rows close together want the four (24 at 64: 39 / 55).
+        if (tuned && bytes > kFillBytes && !(revisits && !in.unpack)) {
+            const bool apart = inner_pitch >= 2 * kLineBytes && inner_pitch >= 2 * run;
+            if (run >= 512 || in.unpack || (apart && (run >= 64 || (inner_pitch % 512 == 0 && inner_pitch < kPageBytes)))) ur_short = 1;
+            // whole-line rows written through as well: 128 at 512 24.8 -> 23.8, 512 at 1024 24.6 -> 24.0
+            if (in.unpack && !partial_rows && dims.size() > 1 && run <= 512) nt = 7;
+        }
+    }
+    // Loads without the streaming hint leave the source in the Infinity Cache, where the next reader finds it: worth it
+    // while the source is a small part of its 256 MiB.  Measured with three 64 MiB sources in turn (they all
+    // stay): packing and unpacking dense rows 22.7 -> 19.2 us, 100-byte rows at 512 25.4 -> 23.3 and 39.9 -> 34.3;
+    // with twelve (none stays) 23.7 -> 24.1, 26.4 -> 27.3, 39.9 -> 41.2.
+    bool keep = false;
+    if (in.nt < 0 && !(in.unpack && in.packed_on_host)) {
+        int64_t footprint = bytes;   // of the source, in whole memory lines
+        if (!in.unpack && dims.size() > 1)
+            footprint = inner_pitch < kLineBytes ? rows * std::max(inner_pitch, run)
+                                                 : rows * ((run + kLineBytes - 1) / kLineBytes * kLineBytes);
+        // sparse rows at wide, even distances share few of the cache's sets: 12 at 2048, 64 MB of lines: 13.5 -> 15.1
+        const bool sparse = !in.unpack && inner_pitch >= 512 && run < kLineBytes;
+        // memory that the same request comes back to is worth keeping whatever its size (300 nested objects whose boxes
+        // overlap: 201 -> 186)
+        keep = footprint <= (sparse ? kKeepBytes / 2 : kKeepBytes) || (revisits && !in.unpack);
     }
     if (in.nt >= 0) nt = in.nt;
     if (in.max_ur == 1 || in.max_ur == 4) ur_short = in.max_ur;
     Splitter s{in, word_log2, run, out, ur_short, nt, in.grid > 0 ? static_cast<uint32_t>(in.grid) : 0u};
     s.split_runs(dims, typed, in.packed);
+    for (Launch& l : *out) l.keep = keep;
     return kSuccess;
 }
 
@@ -587,6 +648,7 @@ std::string describe(const std::vector<Launch>& launches) {
             std::snprintf(line, sizeof line, " grid=%u", l.grid);
             text += line;
         }
+        if (l.keep) text += " keep";
         text += "\n";
     }
     return text;

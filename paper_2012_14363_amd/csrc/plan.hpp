@@ -106,6 +106,8 @@ struct Launch {
     int ur = 1;         // rows per thread
     int nt = 3;         // streaming hints: bit 0 = non-temporal loads, bit 1 = non-temporal stores,
                         // bit 2 (with bit 1) = stores that L2 writes through at once
+    bool keep = false;  // plain loads in spite of bit 0: the source is small enough to stay in the Infinity Cache
+    int hints() const { return keep ? nt & ~1 : nt; }
     uint32_t nblocks = 0;  // tiles
     uint32_t grid = 0;     // workgroups launched; 0 = one per tile
 };

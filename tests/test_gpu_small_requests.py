@@ -44,6 +44,6 @@ def test_data_is_there_when_the_call_returns(workgroups, unpack):
                 got = typed.to("cpu").numpy()
             want = typed_h.copy()
             cc.unpack(packed_h, 0, want, 3, 1, recipe)
-        assert f"blocks={workgroups}\n" in tp.last_plan() and tp.last_plan().count("\n") == 1, tp.last_plan()
+        assert f"blocks={workgroups} " in tp.last_plan() and tp.last_plan().count("\n") == 1, tp.last_plan()
         assert np.array_equal(got, want)
     tp.type_free(h)
