@@ -239,7 +239,7 @@ int run_launches(const std::vector<Launch>& launches, bool unpack, hipStream_t s
     // (the "nt" override asks for other stores than a launch that signals for itself can have)
     if (launches.size() == 1 && signals_itself(launches[0]) && g_nt.load(std::memory_order_relaxed) < 0) {
         Signal signal;
-        if (signal.take(launches[0].nblocks)) {
+        if (signal.take(launches[0].nblocks, stream)) {
             const hipError_t e = enqueue_signalled(launches[0], unpack, stream, signal.params());
             if (e == hipSuccess) return outcome(signal.wait(stream));
             signal.cancel();

@@ -84,14 +84,18 @@ uint32_t* counters_of(Slots& s, int device) {
 
 }  // namespace
 
-bool Signal::take(uint32_t workgroups) {
+bool Signal::take(uint32_t workgroups, hipStream_t stream) {
     Slots& s = slots();
-    if (!s.ready.load(std::memory_order_acquire) && !prepare(s)) return false;
     int device = -1;
-    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) {
+    hipDevice_t runs_on = -1;
+    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices ||
+        hipStreamGetDevice(stream, &runs_on) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
+    // A kernel runs on its stream's GPU, whatever the thread's current one is, and the counter has to be that GPU's own.
+    if (runs_on != device) return false;
+    if (!s.ready.load(std::memory_order_acquire) && !prepare(s)) return false;
     uint32_t* counters = counters_of(s, device);
     if (!counters) return false;
     uint32_t free = s.free.load(std::memory_order_relaxed);

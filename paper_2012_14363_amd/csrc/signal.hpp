@@ -35,8 +35,9 @@ public:
     Signal(const Signal&) = delete;
     Signal& operator=(const Signal&) = delete;
 
-    // Takes a slot for a launch of `workgroups` on the current device; false if there is none to be had.
-    bool take(uint32_t workgroups);
+    // Takes a slot for a launch of `workgroups` on `stream`; false if there is none to be had or the stream is of
+    // another GPU than the current one (its kernels could not reach this one's counter).
+    bool take(uint32_t workgroups, hipStream_t stream);
     const SignalParams& params() const { return params_; }
     // The launch was refused: the slot is as it was before.
     void cancel();

@@ -47,3 +47,24 @@ def test_data_is_there_when_the_call_returns(workgroups, unpack):
         assert f"blocks={workgroups} " in tp.last_plan() and tp.last_plan().count("\n") == 1, tp.last_plan()
         assert np.array_equal(got, want)
     tp.type_free(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs a stream of another GPU")
+def test_stream_of_another_gpu_than_the_current_one():
+    other = torch.device("cuda:1")
+    rows = 4 * ROWS_PER_WORKGROUP[False]
+    recipe = hvector(rows, 1, 128, contiguous(100, BYTE))
+    h = tp.type_from_recipe(recipe)
+    size = tp.type_size(h)
+    typed_h = W.random_bytes(90, rows * 128)
+    with torch.cuda.device(other):
+        typed, stream = torch.from_numpy(typed_h).to(other), torch.cuda.Stream()
+        torch.cuda.synchronize()
+    out = torch.full((size,), 0xEE, dtype=torch.uint8).pin_memory()
+    with torch.cuda.device(0):
+        assert tp.pack(typed, 1, h, out, size, 0, stream=stream) == size
+    want = np.full(size, 0xEE, np.uint8)
+    cc.pack(typed_h, 0, 1, recipe, want, 0)
+    assert np.array_equal(out.numpy(), want)
+    tp.type_free(h)
