@@ -136,13 +136,13 @@ __global__ void __launch_bounds__(kBlockThreads) prefetch_kernel(PrefetchParams 
 }
 
 // Transposing tiles through LDS (tile_body.hpp: xpose_phase).
-template <int WLOG2, bool UNPACK, bool SQUARE>
+template <int WLOG2, bool UNPACK, bool SQUARE, int NT>
 __global__ void __launch_bounds__(kBlockThreads) xpose_kernel(XParams p) {
     using W = typename WordOf<WLOG2>::type;
     __shared__ W lds[XposeTile<WLOG2>::kLdsWords];
-    xpose_phase<WLOG2, UNPACK, true, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<3>{}, lds);
+    xpose_phase<WLOG2, UNPACK, true, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<NT>{}, lds);
     __syncthreads();
-    xpose_phase<WLOG2, UNPACK, false, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<3>{}, lds);
+    xpose_phase<WLOG2, UNPACK, false, SQUARE>(p, blockIdx.x, threadIdx.x, DeviceMem<NT>{}, lds);
 }
 
 // Puts a kernel of by-value parameters on the stream.
@@ -154,8 +154,9 @@ hipError_t launch(void (*fn)(P...), uint32_t grid, hipStream_t stream, const P&.
 
 template <int WLOG2, bool UNPACK>
 hipError_t launch_xpose(const Launch& l, hipStream_t stream) {
-    if (xpose_is_square(l.x, WLOG2)) return launch(xpose_kernel<WLOG2, UNPACK, true>, l.nblocks, stream, l.x);
-    return launch(xpose_kernel<WLOG2, UNPACK, false>, l.nblocks, stream, l.x);
+    const bool square = xpose_is_square(l.x, WLOG2);
+    if (l.keep) return launch(square ? xpose_kernel<WLOG2, UNPACK, true, 2> : xpose_kernel<WLOG2, UNPACK, false, 2>, l.nblocks, stream, l.x);
+    return launch(square ? xpose_kernel<WLOG2, UNPACK, true, 3> : xpose_kernel<WLOG2, UNPACK, false, 3>, l.nblocks, stream, l.x);
 }
 
 template <bool UNPACK>
@@ -179,9 +180,9 @@ hipError_t enqueue_xpose(const Launch& l, hipStream_t stream) {
 // the descriptor that owns it (binary search over at most 40 block ranges, scalar)
 // and runs the same tile body.  Saves one launch per datatype where launches are
 // short, e.g. the 26 regions of a halo exchange.
-template <bool UNPACK>
+template <bool UNPACK, int NT>
 __global__ void __launch_bounds__(kBlockThreads) batch_kernel(BatchParams b) {
-    batch_thread<UNPACK>(b, blockIdx.x, threadIdx.x, DeviceMem<3>{});
+    batch_thread<UNPACK>(b, blockIdx.x, threadIdx.x, DeviceMem<NT>{});
 }
 
 using KernelFn = void (*)(KParams);
@@ -302,7 +303,8 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
 
 hipError_t enqueue_batch(const BatchParams& b, bool unpack, hipStream_t stream) {
     if (b.n == 0 || b.nblocks == 0 || b.nblocks > kMaxGrid) return hipErrorInvalidValue;
-    return launch(unpack ? batch_kernel<true> : batch_kernel<false>, b.nblocks, stream, b);
+    if (b.keep) return launch(unpack ? batch_kernel<true, 2> : batch_kernel<false, 2>, b.nblocks, stream, b);
+    return launch(unpack ? batch_kernel<true, 3> : batch_kernel<false, 3>, b.nblocks, stream, b);
 }
 
 }  // namespace tp
