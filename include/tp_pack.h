@@ -23,9 +23,7 @@
  *     memory and the library keeps no per-type metadata on the device:
  *     everything a kernel needs travels in its kernel arguments (Sec. 3.3,
  *     last paragraph).  Only the resource cache, the staged host delivery
- *     without a caller's staging buffer and tp_model_measure allocate (and the
- *     first synchronous call one page of pinned host memory, kept for the
- *     completion flags of small requests).
+ *     without a caller's staging buffer and tp_model_measure allocate.
  *   - Thread safety: the handle table is guarded by a mutex; pack/unpack calls
  *     may run concurrently on distinct streams.
  *   - There is no CPU fallback: pack/unpack need a working HIP device and
@@ -140,8 +138,8 @@ int tp_pack_size(int incount, tp_type t, int64_t *size);
  * stride or run length; speed does not depend on it beyond a few percent.  `hip_stream` is a
  * hipStream_t (NULL = the default stream).
  *
- * tp_pack / tp_unpack return after the data is complete (they wait for their work on the stream, and so
- * for all work before it, as the paper's timed region does, Sec. 6.3).  The *_async forms only enqueue on the stream; the
+ * tp_pack / tp_unpack return after the data is complete (they synchronize the stream, as the
+ * paper's timed region does, Sec. 6.3).  The *_async forms only enqueue on the stream; the
  * caller synchronizes.  A call may enqueue several kernels (a very large request is split; an
  * unpack of half a million or more tiny rows alternates read-only passes over its packed bytes with
  * the passes that store them), all on `hip_stream` and in order; none allocates or records a

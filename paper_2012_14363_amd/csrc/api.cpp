@@ -16,7 +16,6 @@
 #include "kernels.hpp"
 #include "plan.hpp"
 #include "resource_cache.hpp"
-#include "signal.hpp"
 #include "status.hpp"
 #include "transfer.hpp"
 #include "type_tree.hpp"
@@ -236,16 +235,6 @@ int enqueue_launches(const std::vector<Launch>& launches, bool unpack, hipStream
 
 // The same, and waits for them.
 int run_launches(const std::vector<Launch>& launches, bool unpack, hipStream_t stream) {
-    // (the "nt" override asks for other stores than a launch that signals for itself can have)
-    if (launches.size() == 1 && signals_itself(launches[0]) && g_nt.load(std::memory_order_relaxed) < 0) {
-        Signal signal;
-        if (signal.take(launches[0].nblocks, stream)) {
-            const hipError_t e = enqueue_signalled(launches[0], unpack, stream, signal.params());
-            if (e == hipSuccess) return outcome(signal.wait(stream));
-            signal.cancel();
-            return outcome(e);
-        }
-    }
     const int rc = enqueue_launches(launches, unpack, stream);
     return rc == kSuccess ? outcome(hipStreamSynchronize(stream)) : rc;
 }

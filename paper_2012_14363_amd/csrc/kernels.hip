@@ -37,8 +37,7 @@ namespace {
 // stores can carry the non-temporal bit (`nt`): the data then does not displace
 // other lines in L2 / Infinity Cache.  NT bit 0: loads, bit 1: stores, bit 2: stores
 // also carry `sc1`, which has L2 write them through at once instead of holding the
-// line until something evicts it; bit 3: stores carry `sc0 sc1`, system scope: written
-// through as well, and waiting for the store is waiting until every agent can see it.
+// line until something evicts it.
 // The word is accessed through a type of alignment 1: the address may be any byte, and
 // the compiler, which knows that this target takes unaligned accesses, still emits one
 // global_load/store of the full width.
@@ -53,8 +52,7 @@ struct DeviceMem {
     template <class W>
     __device__ __forceinline__ void store(char* p, const W& v) const {
         typedef W Unaligned __attribute__((aligned(1)));
-        if constexpr (NT & 8) store_visible(p, v);
-        else if constexpr (NT & 4) store_through(p, v);
+        if constexpr (NT & 4) store_through(p, v);
         else if constexpr (NT & 2) __builtin_nontemporal_store(v, reinterpret_cast<Unaligned*>(p));
         else *reinterpret_cast<Unaligned*>(p) = v;
     }
@@ -80,20 +78,6 @@ struct DeviceMem {
         else
             asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
     }
-    // `global_store ... sc0 sc1 nt`, likewise.
-    template <class W>
-    __device__ __forceinline__ static void store_visible(char* p, const W& v) {
-        if constexpr (sizeof(W) == 1)
-            asm volatile("global_store_byte %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(static_cast<uint32_t>(v)) : "memory");
-        else if constexpr (sizeof(W) == 2)
-            asm volatile("global_store_short %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(static_cast<uint32_t>(v)) : "memory");
-        else if constexpr (sizeof(W) == 4)
-            asm volatile("global_store_dword %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
-        else if constexpr (sizeof(W) == 8)
-            asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
-        else
-            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
-    }
 };
 
 template <int WLOG2, int UX, int UR, bool UNPACK, int NRD, int NT>
@@ -101,23 +85,6 @@ __global__ void __launch_bounds__(kBlockThreads) tile_kernel(KParams p) {
     // one workgroup per tile, or (staged unpack) fewer workgroups that each take every gridDim.x-th tile
     for (uint32_t tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x)
         tile_thread<WLOG2, UX, UR, UNPACK, NRD>(p, tile, threadIdx.x, DeviceMem<NT>{});
-}
-
-// The end of a workgroup of a launch that signals for itself (signal.hpp).  All its stores were of system
-// scope, so a wave that has waited for them knows they are where every agent sees them; once every wave of the
-// workgroup has, the workgroup counts itself, and the launch's last one tells the host.
-__device__ __forceinline__ void signal_done(const SignalParams& s) {
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    if (s.counter && __hip_atomic_fetch_add(s.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != s.last) return;
-    __hip_atomic_store(s.flag, s.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-template <int WLOG2, int UX, int UR, bool UNPACK, int NRD>
-__global__ void __launch_bounds__(kBlockThreads) signalled_kernel(BatchDesc d, SignalParams s) {
-    tile_thread<WLOG2, UX, UR, UNPACK, NRD>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<10>{});
-    signal_done(s);
 }
 
 // The launches that are most of a program's calls: one tile per workgroup, at most three row dimensions.  Their
@@ -206,16 +173,7 @@ struct PickKernel {
     }
 };
 
-// Visitors for the compact launches.
-template <bool UNPACK>
-struct PickSignalled {
-    void (*fn)(BatchDesc, SignalParams) = nullptr;
-    template <int WLOG2, int UX, int UR, int NRD>
-    void operator()() {
-        fn = signalled_kernel<WLOG2, UX, UR, UNPACK, NRD ? NRD : kBatchRowDims>;
-    }
-};
-
+// Visitor for the compact launches.
 template <bool UNPACK>
 struct PickCompact {
     int nt = 3;
@@ -234,27 +192,7 @@ struct PickCompact {
 // Whether a launch can have its parameters in a BatchDesc.
 bool fits_compact(const Launch& l) { return l.kind == kTile && l.grid == 0 && l.p.nrd <= static_cast<uint32_t>(kBatchRowDims); }
 
-constexpr uint32_t kSignalledBlocks = 256;
-
 }  // namespace
-
-bool signals_itself(const Launch& l) {
-    return fits_compact(l) && l.nblocks > 0 && l.nblocks <= kSignalledBlocks;
-}
-
-hipError_t enqueue_signalled(const Launch& l, bool unpack, hipStream_t stream, const SignalParams& signal) {
-    if (!signals_itself(l) || !signal.flag || (l.nblocks > 1) != (signal.counter != nullptr)) return hipErrorInvalidValue;
-    void (*fn)(BatchDesc, SignalParams) = nullptr;
-    if (unpack) {
-        PickSignalled<true> pick;
-        if (dispatch_launch(l, l.p.nrd, pick)) fn = pick.fn;
-    } else {
-        PickSignalled<false> pick;
-        if (dispatch_launch(l, l.p.nrd, pick)) fn = pick.fn;
-    }
-    if (!fn) return hipErrorInvalidValue;
-    return launch(fn, l.nblocks, stream, compact(l), signal);
-}
 
 hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
     if (l.nblocks == 0 || l.grid > l.nblocks || (l.grid ? l.grid : l.nblocks) > kMaxGrid) return hipErrorInvalidValue;

@@ -1,6 +1,5 @@
-"""Synchronous calls of small requests, whose kernel tells the host itself that it is done: what the call has
-written is there when it returns, for the host and for another stream, around the number of workgroups up to
-which that holds (the last count here takes the other way)."""
+"""Synchronous calls of small requests: what the call has written is there when it returns, for the host and for
+another stream, and its stream is idle, around 256 workgroups (one for each CU)."""
 import numpy as np
 import pytest
 
@@ -47,6 +46,43 @@ def test_data_is_there_when_the_call_returns(workgroups, unpack):
         assert f"blocks={workgroups} " in tp.last_plan() and tp.last_plan().count("\n") == 1, tp.last_plan()
         assert np.array_equal(got, want)
     tp.type_free(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("workgroups", (1, 256, 257))
+@pytest.mark.parametrize("unpack", (False, True))
+def test_the_stream_is_synchronized_when_the_call_returns(workgroups, unpack):
+    """Work enqueued before the call is complete as well: an event recorded in front of it has happened, the stream
+    has nothing left, and what an earlier enqueue-only call stored is there for the host and for another stream."""
+    dev = torch.device("cuda:0")
+    rows, many = ROWS_PER_WORKGROUP[unpack] * workgroups - 3, 1 << 16
+    print("stream after a synchronous call, workgroups", workgroups, "unpack", unpack, flush=True)
+    small, large = (tp.type_from_recipe(hvector(n, 1, 128, contiguous(100, BYTE))) for n in (rows, many))
+    typed_h = W.random_bytes(60, many * 128)
+    typed = torch.from_numpy(typed_h).to(dev)
+    packed, target = torch.zeros(100 * rows, dtype=torch.uint8, device=dev), torch.zeros(128 * rows, dtype=torch.uint8, device=dev)
+    want = np.zeros(100 * many, np.uint8)
+    cc.pack(typed_h, 0, 1, hvector(many, 1, 128, contiguous(100, BYTE)), want, 0)
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for k in range(20):
+        earlier = torch.zeros(100 * many, dtype=torch.uint8, device=dev)
+        on_host = torch.zeros(100 * many, dtype=torch.uint8).pin_memory()
+        torch.cuda.synchronize()
+        before = torch.cuda.Event()
+        with torch.cuda.stream(stream):
+            assert tp.pack_async(typed, 1, large, on_host if k % 2 else earlier, 100 * many, 0) == 100 * many
+            before.record()
+            if unpack:
+                tp.unpack(packed, 100 * rows, 0, target, 1, small)
+            else:
+                tp.pack(typed, 1, small, packed, 100 * rows, 0)
+        assert before.query() and stream.query()
+        with torch.cuda.stream(other):
+            got = on_host.numpy() if k % 2 else earlier.to("cpu").numpy()
+        assert np.array_equal(got, want)
+    tp.type_free(small)
+    tp.type_free(large)
 
 
 @pytest.mark.gpu
