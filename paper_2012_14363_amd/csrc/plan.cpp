@@ -512,7 +512,7 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
         // 1024: 25.1 -> 23.8, 2408 at 4096: 28.3 -> 24.3, 9000 at 12288: 27.2 -> 24.5), and when packing from
         // rows far apart (100 at 512: 27.9 -> 26.3), short ones where their distance is a multiple of 512 bytes (12 at 512: 46 ->
         // 42, 32 at 512: 52 -> 47; but 20 at 1000: 30.3 -> 31.5); short rows close together want the four (24 at 64: 39 / 55).
-        if (tuned && bytes > kFillBytes && !(revisits && !in.unpack)) {
+        if (tuned && bytes > kFillBytes && !revisits) {
             const bool apart = inner_pitch >= 2 * kLineBytes && inner_pitch >= 2 * run;
             if (run >= 512 || in.unpack || (apart && (run >= 64 || (inner_pitch % 512 == 0 && inner_pitch < kPageBytes)))) ur_short = 1;
             // whole-line rows written through as well: 128 at 512 24.8 -> 23.8, 512 at 1024 24.6 -> 24.0

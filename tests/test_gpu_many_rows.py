@@ -55,3 +55,23 @@ def test_many_rows(run, pitch, rows, offset, unpack_plan, pack_plan):
     cc.unpack(packed_h, 0, want, offset, 1, recipe)
     assert np.array_equal(typed.cpu().numpy(), want)
     tp.type_free(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("elem", (1, 4, 12))
+def test_unpack_of_two_interleaved_columns(elem):
+    """Rows that lie between the rows of another outer index: four per thread, whatever the size."""
+    dev = torch.device("cuda:0")
+    rows = (5 << 20) // elem // 2 + 1
+    recipe = hvector(2, 1, elem, hvector(rows, 1, 2 * elem, contiguous(elem, BYTE)))
+    print("two columns", elem, rows, flush=True)
+    h = tp.type_from_recipe(recipe)
+    size = 2 * rows * elem
+    typed_h, packed_h = W.random_bytes(elem, size + 8), W.random_bytes(rows, size)
+    typed, packed = torch.from_numpy(typed_h).to(dev), torch.from_numpy(packed_h).to(dev)
+    assert tp.unpack(packed, size, 0, typed.data_ptr() + 3, 1, h) == size
+    assert "tile" in tp.last_plan() and " ux=1 ur=4 " in tp.last_plan(), tp.last_plan()
+    want = typed_h.copy()
+    cc.unpack(packed_h, 0, want, 3, 1, recipe)
+    assert np.array_equal(typed.cpu().numpy(), want)
+    tp.type_free(h)
