@@ -462,28 +462,42 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
     if (through && in.stage != 0 && plan_staged(in, dims, typed, out)) return kSuccess;
     if (in.unpack && tuned && in.narrow_partial_rows && partial_rows && outer_pitch >= kLineBytes && rows >= kManyRows &&
         bytes >= kManyBytes) {
-        // Many rows that end in partially written memory lines.  Measured on 24 and 64 MiB of rows of 1 to 65536
-        // bytes at pitches from 5 % above the run to 12 KiB, sources from HBM and from the Infinity Cache, with
-        // every word, one and four rows per thread, and streaming (`nt`) or written-through (`sc1 nt`) stores.
+        // Many rows that end in partially written memory lines.  Measured on 4, 16, 24, 56 and 64 MiB of rows of 1 to 65536
+        // bytes at pitches from one byte above the run to 12 KiB, with every word, one and four rows per thread, and
+        // streaming (`nt`) or written-through (`sc1 nt`) stores.  Pairs joined by "and" are 16 MiB unless said
+        // otherwise, with sources from the Infinity Cache and from HBM behind a kernel that filled it with other data.
+        //   Do rows lie so far apart that L2 has little to merge: 64 bytes, or, beyond 4 MiB, eight times the run (1 at 17
+        // bytes, written through 111 and 114, streaming 129 and 138; 3 at 39: 85 and 89, 97 and 102; but 4 MiB of 2 at 16
+        // 16.0 and 17.2, 12.0 and 17.8)?
+        const bool apart = inner_pitch >= kLineBytes / 2 || (inner_pitch >= 8 * run && bytes > kFillBytes);
         //   Stores: written through L2 at once where a line holds at most two rows and rows are short (128-byte
         // pitch, 64 MiB: 12-byte rows 139 us against 195 streaming, 24: 72 / 100, 48: 41 / 53; 1-KiB pitch,
         // 256-byte rows 39.6 / 42.6).  Streaming where neighbouring rows share their lines, so that L2 can merge
         // them (12-byte rows at 13: 46 / 132, 24 at 25: 40 / 71, 64 at 67: 35 / 38), and for rows beyond 1 KiB
-        // (2408 bytes at 4096: 24.8 / 27.3).
-        //   Word: 17 to 32 lanes on a row of at least 128 bytes, 9 to 16 on a shorter one, and no less than 4 bytes
-        // (128-byte rows at 512, words of 4 / 8 / 16: 45 / 54 / 62; 256-byte rows 46 / 31 / 38; 24-byte rows at 64, 2 / 4: 110 / 70).
+        // (2408 bytes at 4096: 24.8 / 27.3); but for rows of half a line and more only beyond 4 MiB, since what L2 still
+        // holds when a kernel ends is written then (4 MiB, written through / streaming: 96 at 112 6.0 / 6.7, 128 at 129
+        // 5.9 / 6.7, 1500 at 1501 5.8 / 6.6).
+        const bool streams = bytes > kFillBytes || run < kLineBytes / 2;
+        const bool shared_lines = !apart || (inner_pitch >= kLineBytes / 2 && inner_pitch < kLineBytes * 3 / 2 && inner_pitch - run < 32 && streams);
         //   One row per thread, except where rows are so close (or, short ones, so far apart: one address
         // translation each) that four are the better (24 at 25: 40 / 47; 24 at 4096: 13.1 / 16.5).
-        const bool shared_lines = inner_pitch < kLineBytes / 2 || (inner_pitch < kLineBytes * 3 / 2 && inner_pitch - run < 32);
-        //   Rows of whole aligned 64-byte blocks: 8 lanes (64 bytes at 512, words of 4 / 8 / 16: 43.6 / 30.3 / 32.7).
-        const bool blocks = (bits & 63) == 0;
-        const int64_t lanes = blocks ? 8 : run >= kLineBytes ? 32 : inner_pitch < kLineBytes * 3 / 2 && run > 32 ? 8 : 16;
-        // (exceptions: short rows 512 to 1023 bytes apart, 24 at 512, words of 2 / 4: 69 / 83; 12 at 384, 1 / 4: 41.1 / 43.8)
-        const bool narrow = (run <= 32 && inner_pitch >= 512 && inner_pitch < 1024) || (run < 16 && inner_pitch >= 2 * kLineBytes);
-        const int by_lanes = run < 4 ? 0 : narrow ? (run >= 16 ? 1 : 0) : std::max(2, ceil_log2(static_cast<uint64_t>((run + lanes - 1) / lanes)));
+        ur_short = (run <= 32 && !apart) || (run < 64 && inner_pitch >= kPageBytes) ? 4 : 1;
+        nt = ur_short == 1 && !shared_lines && (run <= 1024 || !streams) ? 7 : 3;
+        //   Word.  Rows of at least a line: 16 bytes (200 at 216, words of 8 and of 16: 12.2 and 15.4, 9.3 and 13.3; 192 at 228:
+        // 12.8 and 15.4, 9.5 and 13.7), or 8 for rows of at most two lines at odd addresses and 384 bytes or more apart
+        // (128 at 768: 14.0 and 20.3, 16.5 and 22.8; 56 MiB, 200 at 384: 21.2 and 39.0, 24.6 and 43.8).
+        //   Shorter rows: 5 to 8 lanes on a row where a line holds parts of two rows (words of 1, 2 and 4 bytes: 8 at 128
+        // 52 and 57, 78 and 80, 77 and 82; 16 at 128 43 and 47, 28 and 33, 38 and 43; words of 4 and 8: 48 at 160 18.4 and 22.2,
+        // 17.1 and 22.6), 9 to 16 beyond (24 at 256, words of 2 and 4: 20.3 and 30.4, 23.6 and 30.4; 100 at 512, 4, 8 and 16: 11.6
+        // and 17.5, 9.9 and 16.5, 13.0 and 18.7) and 8 on whole aligned 64-byte blocks (64 at 512, words of 4 / 8 / 16: 43.6 /
+        // 30.3 / 32.7).  No less than 4 bytes for rows closer than that (12 at 13, words of 1 and 4: 13.4 and 20.2, 12.6 and 15.8)
+        // and for those so far apart that their translations decide (4 MiB, 16 at 1024: 14.0 and 16.5, 14.7 and 15.4).
+        const int64_t two_rows = run <= 32 ? 2 * kLineBytes : kLineBytes * 3 / 2;
+        const int64_t lanes = (bits & 63) == 0 || (inner_pitch < two_rows && (apart || run > 32)) ? 8 : 16;
+        int by_lanes = ceil_log2(static_cast<uint64_t>((run + lanes - 1) / lanes));
+        if (run >= kLineBytes) by_lanes = (bits & 15) != 0 && inner_pitch >= 3 * kLineBytes && run <= 2 * kLineBytes ? 3 : 4;
+        else if (run >= 4 && (!apart || (run >= 16 && inner_pitch >= 1024))) by_lanes = std::max(2, by_lanes);
         word_log2 = std::min(word_log2, by_lanes);
-        ur_short = (run <= 32 && inner_pitch < kLineBytes / 2) || (run < 64 && inner_pitch >= kPageBytes) ? 4 : 1;
-        nt = ur_short == 1 && !shared_lines && run <= 1024 ? 7 : 3;
     } else if (through) {
         // Fewer rows than that, closer than a page, that share no line with rows of another outer index: written through
         // L2 at once as well, one row per thread, a row spread over 8 to 15 lanes (32 MiB of rows at 512-byte pitch,

@@ -17,7 +17,21 @@ SHAPES = [
     (33, 66, 40000, 1, "W=8 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
     (40, 191, 30000, 0, "W=8 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
     (40, 192, 30000, 0, "W=4 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
-    (127, 150, 10000, 3, "W=16 ux=1 ur=1 nt=3", "W=16 ux=1 ur=4"),
+    (127, 150, 10000, 3, "W=16 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),  # they share lines, but are at most 4 MiB
+    (127, 150, 34000, 3, "W=16 ux=1 ur=1 nt=3", "W=16 ux=1 ur=4"),
+    (1, 8, 4200000, 3, "W=1 ux=1 ur=1 nt=7", "W=1 ux=1 ur=4"),      # eight times the run apart
+    (1, 8, 4190000, 3, "W=1 ux=1 ur=4 nt=3", "W=1 ux=1 ur=4"),      # at most 4 MiB
+    (7, 55, 600000, 3, "W=4 ux=1 ur=4 nt=3", "W=1 ux=1 ur=4"),      # not quite
+    (7, 56, 600000, 3, "W=1 ux=1 ur=1 nt=7", "W=1 ux=1 ur=4"),
+    (8, 128, 140000, 1, "W=1 ux=1 ur=1 nt=7", "W=2 ux=1 ur=4"),     # bytes: two rows to a line
+    (31, 255, 40000, 1, "W=4 ux=1 ur=1 nt=7", "W=4 ux=1 ur=4"),
+    (32, 257, 40000, 1, "W=2 ux=1 ur=1 nt=7", "W=4 ux=1 ur=4"),
+    (17, 1023, 70000, 1, "W=2 ux=1 ur=1 nt=7", "W=4 ux=1 ur=4"),    # translations decide from 1 KiB on
+    (17, 1024, 70000, 1, "W=4 ux=1 ur=1 nt=7", "W=4 ux=1 ur=4"),
+    (128, 383, 9001, 1, "W=16 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),   # one or two lines at an odd address, below and from 384 on
+    (256, 384, 9001, 1, "W=8 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
+    (257, 385, 9001, 1, "W=16 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
+    (1500, 1501, 2000, 1, "W=16 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
     (129, 512, 9001, 0, "W=8 ux=1 ur=1 nt=7", "W=16 ux=1 ur=4"),
     (24, 600, 50000, 7, "W=2 ux=1 ur=1 nt=7", "W=4 ux=1 ur=4"),
     (12, 300, 90000, 7, "W=1 ux=1 ur=1 nt=7", "W=2 ux=1 ur=4"),
