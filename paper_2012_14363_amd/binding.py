@@ -140,8 +140,8 @@ def lib() -> ctypes.CDLL:
         L.tp_error_string.argtypes = [ctypes.c_int]
         L.tp_error_string.restype = ctypes.c_char_p
         _lib = L
-        _pycall.setup({name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}, _check, _first_stream,
-                      *_stream_getters())
+        _pycall.setup({name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}, _check, _marshal,
+                      _first_stream, *_stream_getters())
     return _lib
 
 
@@ -291,7 +291,8 @@ if _pycall is not None:
 
 
 class Batch:
-    """Marshalled argument arrays of a batched call, reusable across calls (the arrays are built once)."""
+    """Marshalled argument arrays of a batched call, reusable across calls (the arrays are built once; a call reads
+    what they, or others put in their place, hold then)."""
 
     def __init__(self, typed_bufs, counts, types):
         n = len(types)
@@ -300,8 +301,25 @@ class Batch:
         self.ptrs = (ctypes.c_void_p * n)(*[_ptr(b) for b in typed_bufs])
         self.counts = (ctypes.c_int * n)(*counts)
         self.types = (ctypes.c_int32 * n)(*types)
-        # what _pycall reads: the arrays are this object's own and stay where they are
-        self.raw = (n, *(ctypes.addressof(a) for a in (self.ptrs, self.counts, self.types)))
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        self.__dict__["raw"] = None   # what _pycall reads: _marshal makes it when the next call asks
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        self.__dict__["raw"] = None
+
+
+def _marshal(batch):
+    """Batch.raw: (n, address of the pointers, of the counts, of the types, the objects these are of)."""
+    held = (batch.ptrs, batch.counts, batch.types)
+    for kind, array in zip((ctypes.c_void_p, ctypes.c_int, ctypes.c_int32), held):
+        ctypes.POINTER(kind).from_param(array)   # refuses arrays of other types
+    raw = (batch.n, *(ctypes.cast(a, ctypes.c_void_p).value or 0 for a in held), held)
+    if isinstance(batch, Batch):
+        batch.__dict__["raw"] = raw
+    return raw
 
 
 # ------------------------------------------------------------------ model and host delivery

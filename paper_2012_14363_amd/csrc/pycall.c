@@ -34,6 +34,7 @@ static const char *const entry_names[ENTRIES] = {
 static void *entries[ENTRIES];   /* all NULL until setup() */
 
 static PyObject *load_library, *raise_error;    /* binding.lib; raises TpError(code, where) */
+static PyObject *marshal_batch;                 /* binding._marshal */
 static PyObject *first_stream, *get_device, *get_stream;
 static int torch_ready;                         /* torch's GPU state exists in this process */
 static PyObject *s_data_ptr, *s_cuda_stream, *s_raw;
@@ -184,47 +185,59 @@ static PyObject *unpack_call(int entry, const char *name, PyObject *const *args,
 }
 
 /* ---------------------------------------------------------------- batches */
-/* Batch.raw: (n, address of the pointers, of the counts, of the types); the Batch owns the arrays. */
-static int as_batch(PyObject *o, int *n, void **ptrs, void **counts, void **types) {
+/* Batch.raw: (n, address of the pointers, of the counts, of the types, the objects these are of); None once one of
+ * them has been replaced, and then made anew.  *held is the tuple, whose objects live as long as the caller keeps it. */
+static int as_batch(PyObject *o, PyObject **held, int *n, void **ptrs, void **counts, void **types) {
     PyObject *raw = PyObject_GetAttr(o, s_raw);
-    if (!raw) return 0;
-    int ok = PyTuple_Check(raw) && PyTuple_GET_SIZE(raw) == 4;
+    if (!raw) {
+        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return 0;
+        PyErr_Clear();   /* another class with a Batch's attributes */
+    }
+    if (!raw || raw == Py_None) {
+        Py_XDECREF(raw);
+        raw = PyObject_CallOneArg(marshal_batch, o);
+        if (!raw) return 0;
+    }
+    int ok = PyTuple_Check(raw) && PyTuple_GET_SIZE(raw) == 5;
     if (!ok) PyErr_SetString(PyExc_TypeError, "not a Batch");
     ok = ok && as_int(PyTuple_GET_ITEM(raw, 0), n) && as_address(PyTuple_GET_ITEM(raw, 1), ptrs) &&
          as_address(PyTuple_GET_ITEM(raw, 2), counts) && as_address(PyTuple_GET_ITEM(raw, 3), types);
-    Py_DECREF(raw);
+    if (ok) *held = raw;
+    else Py_DECREF(raw);
     return ok;
 }
 
 static PyObject *pack_batch_call(int entry, const char *name, PyObject *const *args, Py_ssize_t nargs, PyObject *kwnames) {
     static const char *const names[] = {"batch", "outbuf", "outsize", "position", "stream"};
-    PyObject *a[5];
+    PyObject *a[5], *held;
     void *ptrs, *counts, *types, *out, *stream;
     int n, rc;
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 5, 4, a) || !ready()) return NULL;
-    if (!as_batch(a[0], &n, &ptrs, &counts, &types) || !as_address(a[1], &out) || !as_i64(a[2], &size) ||
-        !as_i64(a[3], &position) || !as_stream(a[4], &stream))
+    if (!as_address(a[1], &out) || !as_i64(a[2], &size) || !as_i64(a[3], &position) || !as_stream(a[4], &stream) ||
+        !as_batch(a[0], &held, &n, &ptrs, &counts, &types))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
     rc = ((pack_batch_fn)entries[entry])(n, ptrs, counts, types, out, size, &position, stream);
     Py_END_ALLOW_THREADS
+    Py_DECREF(held);
     return outcome(rc, entry, position);
 }
 
 static PyObject *unpack_batch_call(int entry, const char *name, PyObject *const *args, Py_ssize_t nargs, PyObject *kwnames) {
     static const char *const names[] = {"inbuf", "insize", "position", "batch", "stream"};
-    PyObject *a[5];
+    PyObject *a[5], *held;
     void *ptrs, *counts, *types, *in, *stream;
     int n, rc;
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 5, 4, a) || !ready()) return NULL;
-    if (!as_address(a[0], &in) || !as_i64(a[1], &size) || !as_i64(a[2], &position) ||
-        !as_batch(a[3], &n, &ptrs, &counts, &types) || !as_stream(a[4], &stream))
+    if (!as_address(a[0], &in) || !as_i64(a[1], &size) || !as_i64(a[2], &position) || !as_stream(a[4], &stream) ||
+        !as_batch(a[3], &held, &n, &ptrs, &counts, &types))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
     rc = ((unpack_batch_fn)entries[entry])(n, in, size, &position, ptrs, counts, types, stream);
     Py_END_ALLOW_THREADS
+    Py_DECREF(held);
     return outcome(rc, entry, position);
 }
 
@@ -302,12 +315,12 @@ static PyObject *py_pack_host_static(PyObject *self, PyObject *const *args, Py_s
     return pack_call(PACK_HOST_STATIC, "pack_host_static", a, a[6] ? 7 : 6, NULL);   /* pack's arguments under another name */
 }
 
-/* setup(addresses, raise_error, first_stream, get_device, get_stream): called by binding.lib() */
+/* setup(addresses, raise_error, marshal, first_stream, get_device, get_stream): called by binding.lib() */
 static PyObject *py_setup(PyObject *self, PyObject *args) {
-    PyObject *addresses, *err, *first, *dev, *str;
+    PyObject *addresses, *err, *batch, *first, *dev, *str;
     void *found[ENTRIES];
     (void)self;
-    if (!PyArg_ParseTuple(args, "O!OOOO", &PyDict_Type, &addresses, &err, &first, &dev, &str)) return NULL;
+    if (!PyArg_ParseTuple(args, "O!OOOOO", &PyDict_Type, &addresses, &err, &batch, &first, &dev, &str)) return NULL;
     for (int i = 0; i < ENTRIES; ++i) {
         PyObject *v = PyDict_GetItemString(addresses, entry_names[i]);
         if (!v) {
@@ -316,9 +329,10 @@ static PyObject *py_setup(PyObject *self, PyObject *args) {
         }
         if (!as_address(v, &found[i])) return NULL;
     }
-    Py_INCREF(err), Py_INCREF(first), Py_INCREF(dev), Py_INCREF(str);
-    Py_XDECREF(raise_error), Py_XDECREF(first_stream), Py_XDECREF(get_device), Py_XDECREF(get_stream);
-    raise_error = err, first_stream = first, get_device = dev, get_stream = str;
+    Py_INCREF(err), Py_INCREF(batch), Py_INCREF(first), Py_INCREF(dev), Py_INCREF(str);
+    Py_XDECREF(raise_error), Py_XDECREF(marshal_batch);
+    Py_XDECREF(first_stream), Py_XDECREF(get_device), Py_XDECREF(get_stream);
+    raise_error = err, marshal_batch = batch, first_stream = first, get_device = dev, get_stream = str;
     torch_ready = 0;
     for (int i = 0; i < ENTRIES; ++i) entries[i] = found[i];
     Py_RETURN_NONE;
@@ -357,7 +371,7 @@ static PyMethodDef methods[] = {
     FAST(pack_host_static, "pack_host_static($module, inbuf, incount, t, host_outbuf, outsize, position, stream=None)\n--\n\n"
                            "tp_pack_host_static (staged through the library's fixed device array; allocates nothing); "
                            "returns the new position."),
-    {"setup", py_setup, METH_VARARGS, "setup(addresses, raise_error, first_stream, get_device, get_stream)"},
+    {"setup", py_setup, METH_VARARGS, "setup(addresses, raise_error, marshal, first_stream, get_device, get_stream)"},
     {"on_first_use", py_on_first_use, METH_O, "on_first_use(loader): what loads the library when the first call needs it"},
     {NULL, NULL, 0, NULL}};
 
