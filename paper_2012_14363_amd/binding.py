@@ -140,7 +140,7 @@ def lib() -> ctypes.CDLL:
         L.tp_error_string.argtypes = [ctypes.c_int]
         L.tp_error_string.restype = ctypes.c_char_p
         _lib = L
-        _pycall.setup({name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}, _check, _marshal,
+        _pycall.setup({name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}, _check, _scalar, _marshal,
                       _first_stream, *_stream_getters())
     return _lib
 
@@ -320,6 +320,16 @@ def _marshal(batch):
     if isinstance(batch, Batch):
         batch.__dict__["raw"] = raw
     return raw
+
+
+def _scalar(value, wide):
+    """The number a ctypes object stands for as an argument: c_int64 (wide) or c_int, or an object that names one."""
+    if isinstance(value, ctypes.c_int64 if wide else ctypes.c_int):
+        return value.value
+    if hasattr(value, "_as_parameter_"):
+        inner = value._as_parameter_
+        return inner if hasattr(inner, "__index__") else _scalar(inner, wide)
+    raise TypeError(f"a whole number is needed, not {type(value).__name__}")
 
 
 # ------------------------------------------------------------------ model and host delivery

@@ -34,7 +34,7 @@ static const char *const entry_names[ENTRIES] = {
 static void *entries[ENTRIES];   /* all NULL until setup() */
 
 static PyObject *load_library, *raise_error;    /* binding.lib; raises TpError(code, where) */
-static PyObject *marshal_batch;                 /* binding._marshal */
+static PyObject *plain_number, *marshal_batch;  /* binding._scalar, binding._marshal */
 static PyObject *first_stream, *get_device, *get_stream;
 static int torch_ready;                         /* torch's GPU state exists in this process */
 static PyObject *s_data_ptr, *s_cuda_stream, *s_raw;
@@ -62,12 +62,24 @@ static int as_i64(PyObject *o, int64_t *v) {
     return 1;
 }
 
+/* An argument of the C call: a whole number, or the ctypes object that stands for one (wide: c_int64, else c_int). */
+static int as_argument(PyObject *o, int wide, int64_t *v) {
+    if (PyIndex_Check(o)) return as_i64(o, v);
+    PyObject *r = PyObject_CallFunction(plain_number, "Oi", o, wide);
+    if (!r) return 0;
+    const int ok = as_i64(r, v);
+    Py_DECREF(r);
+    return ok;
+}
+
 static int as_int(PyObject *o, int *v) {
     int64_t w;
-    if (!as_i64(o, &w)) return 0;
+    if (!as_argument(o, 0, &w)) return 0;
     *v = (int)(uint32_t)(uint64_t)w;
     return 1;
 }
+
+static int as_size(PyObject *o, int64_t *v) { return as_argument(o, 1, v); }
 
 /* A raw address, or anything with data_ptr(). */
 static int as_address(PyObject *o, void **p) {
@@ -160,7 +172,7 @@ static PyObject *pack_call(int entry, const char *name, PyObject *const *args, P
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 7, 6, a) || !ready()) return NULL;
     if (!as_address(a[0], &in) || !as_int(a[1], &count) || !as_int(a[2], &type) || !as_address(a[3], &out) ||
-        !as_i64(a[4], &size) || !as_i64(a[5], &position) || !as_stream(a[6], &stream))
+        !as_size(a[4], &size) || !as_i64(a[5], &position) || !as_stream(a[6], &stream))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
     rc = ((pack_fn)entries[entry])(in, count, type, out, size, &position, stream);
@@ -175,7 +187,7 @@ static PyObject *unpack_call(int entry, const char *name, PyObject *const *args,
     int count, type, rc;
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 7, 6, a) || !ready()) return NULL;
-    if (!as_address(a[0], &in) || !as_i64(a[1], &size) || !as_i64(a[2], &position) || !as_address(a[3], &out) ||
+    if (!as_address(a[0], &in) || !as_size(a[1], &size) || !as_i64(a[2], &position) || !as_address(a[3], &out) ||
         !as_int(a[4], &count) || !as_int(a[5], &type) || !as_stream(a[6], &stream))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
@@ -214,7 +226,7 @@ static PyObject *pack_batch_call(int entry, const char *name, PyObject *const *a
     int n, rc;
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 5, 4, a) || !ready()) return NULL;
-    if (!as_address(a[1], &out) || !as_i64(a[2], &size) || !as_i64(a[3], &position) || !as_stream(a[4], &stream) ||
+    if (!as_address(a[1], &out) || !as_size(a[2], &size) || !as_i64(a[3], &position) || !as_stream(a[4], &stream) ||
         !as_batch(a[0], &held, &n, &ptrs, &counts, &types))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
@@ -231,7 +243,7 @@ static PyObject *unpack_batch_call(int entry, const char *name, PyObject *const 
     int n, rc;
     int64_t size, position;
     if (!collect(name, args, nargs, kwnames, names, 5, 4, a) || !ready()) return NULL;
-    if (!as_address(a[0], &in) || !as_i64(a[1], &size) || !as_i64(a[2], &position) || !as_stream(a[4], &stream) ||
+    if (!as_address(a[0], &in) || !as_size(a[1], &size) || !as_i64(a[2], &position) || !as_stream(a[4], &stream) ||
         !as_batch(a[3], &held, &n, &ptrs, &counts, &types))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
@@ -252,7 +264,7 @@ static int as_host_tail(PyObject **a, void **staging, int64_t *staging_size, int
     *staging = NULL;
     *staging_size = 0;
     *method = TP_METHOD_AUTO;
-    return (!a[0] || a[0] == Py_None || as_address(a[0], staging)) && (!a[1] || as_i64(a[1], staging_size)) &&
+    return (!a[0] || a[0] == Py_None || as_address(a[0], staging)) && (!a[1] || as_size(a[1], staging_size)) &&
            (!a[2] || as_int(a[2], method)) && as_stream(a[3], stream);
 }
 
@@ -266,7 +278,7 @@ static PyObject *py_pack_host(PyObject *self, PyObject *const *args, Py_ssize_t 
     (void)self;
     if (!collect("pack_host", args, nargs, kwnames, names, 10, 6, a) || !ready()) return NULL;
     if (!as_address(a[0], &in) || !as_int(a[1], &count) || !as_int(a[2], &type) || !as_address(a[3], &out) ||
-        !as_i64(a[4], &size) || !as_i64(a[5], &position) || !as_host_tail(a + 6, &staging, &staging_size, &method, &stream))
+        !as_size(a[4], &size) || !as_i64(a[5], &position) || !as_host_tail(a + 6, &staging, &staging_size, &method, &stream))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
     rc = ((pack_host_fn)entries[PACK_HOST])(in, count, type, out, size, &position, staging, staging_size, method, stream, &used);
@@ -283,7 +295,7 @@ static PyObject *py_unpack_host(PyObject *self, PyObject *const *args, Py_ssize_
     int64_t size, position, staging_size;
     (void)self;
     if (!collect("unpack_host", args, nargs, kwnames, names, 10, 6, a) || !ready()) return NULL;
-    if (!as_address(a[0], &in) || !as_i64(a[1], &size) || !as_i64(a[2], &position) || !as_address(a[3], &out) ||
+    if (!as_address(a[0], &in) || !as_size(a[1], &size) || !as_i64(a[2], &position) || !as_address(a[3], &out) ||
         !as_int(a[4], &count) || !as_int(a[5], &type) || !as_host_tail(a + 6, &staging, &staging_size, &method, &stream))
         return NULL;
     Py_BEGIN_ALLOW_THREADS
@@ -315,12 +327,12 @@ static PyObject *py_pack_host_static(PyObject *self, PyObject *const *args, Py_s
     return pack_call(PACK_HOST_STATIC, "pack_host_static", a, a[6] ? 7 : 6, NULL);   /* pack's arguments under another name */
 }
 
-/* setup(addresses, raise_error, marshal, first_stream, get_device, get_stream): called by binding.lib() */
+/* setup(addresses, raise_error, scalar, marshal, first_stream, get_device, get_stream): called by binding.lib() */
 static PyObject *py_setup(PyObject *self, PyObject *args) {
-    PyObject *addresses, *err, *batch, *first, *dev, *str;
+    PyObject *addresses, *err, *number, *batch, *first, *dev, *str;
     void *found[ENTRIES];
     (void)self;
-    if (!PyArg_ParseTuple(args, "O!OOOOO", &PyDict_Type, &addresses, &err, &batch, &first, &dev, &str)) return NULL;
+    if (!PyArg_ParseTuple(args, "O!OOOOOO", &PyDict_Type, &addresses, &err, &number, &batch, &first, &dev, &str)) return NULL;
     for (int i = 0; i < ENTRIES; ++i) {
         PyObject *v = PyDict_GetItemString(addresses, entry_names[i]);
         if (!v) {
@@ -329,10 +341,10 @@ static PyObject *py_setup(PyObject *self, PyObject *args) {
         }
         if (!as_address(v, &found[i])) return NULL;
     }
-    Py_INCREF(err), Py_INCREF(batch), Py_INCREF(first), Py_INCREF(dev), Py_INCREF(str);
-    Py_XDECREF(raise_error), Py_XDECREF(marshal_batch);
+    Py_INCREF(err), Py_INCREF(number), Py_INCREF(batch), Py_INCREF(first), Py_INCREF(dev), Py_INCREF(str);
+    Py_XDECREF(raise_error), Py_XDECREF(plain_number), Py_XDECREF(marshal_batch);
     Py_XDECREF(first_stream), Py_XDECREF(get_device), Py_XDECREF(get_stream);
-    raise_error = err, marshal_batch = batch, first_stream = first, get_device = dev, get_stream = str;
+    raise_error = err, plain_number = number, marshal_batch = batch, first_stream = first, get_device = dev, get_stream = str;
     torch_ready = 0;
     for (int i = 0; i < ENTRIES; ++i) entries[i] = found[i];
     Py_RETURN_NONE;
@@ -371,7 +383,7 @@ static PyMethodDef methods[] = {
     FAST(pack_host_static, "pack_host_static($module, inbuf, incount, t, host_outbuf, outsize, position, stream=None)\n--\n\n"
                            "tp_pack_host_static (staged through the library's fixed device array; allocates nothing); "
                            "returns the new position."),
-    {"setup", py_setup, METH_VARARGS, "setup(addresses, raise_error, marshal, first_stream, get_device, get_stream)"},
+    {"setup", py_setup, METH_VARARGS, "setup(addresses, raise_error, scalar, marshal, first_stream, get_device, get_stream)"},
     {"on_first_use", py_on_first_use, METH_O, "on_first_use(loader): what loads the library when the first call needs it"},
     {NULL, NULL, 0, NULL}};
 

@@ -62,3 +62,19 @@ def test_anything_with_the_attributes_of_a_batch_is_one():
     assert both(Mine()) == TP_ERR_BUFFER
     Mine.counts = (ctypes.c_int * 1)(0)
     assert both(Mine()) == 0
+
+
+def test_ctypes_numbers_are_numbers():
+    t = tp.PREDEFINED["BYTE"]
+
+    class Names:
+        _as_parameter_ = t
+
+    for number in (t, ctypes.c_int32(t), Names(), ctypes.c_int(t)):
+        assert outcome(tp.pack, 0, ctypes.c_int(4), number, 0, ctypes.c_int64(8), 0, 0) == TP_ERR_BUFFER
+        assert outcome(tp.unpack_async, 0, ctypes.c_int64(2), 0, 0, 4, number, 0) == TP_ERR_TRUNCATE
+        assert tp.pack_async(0, ctypes.c_int(0), number, 0, 8, 3, 0) == 3
+    for wrong in (1.0, "1", None, ctypes.c_int16(1), ctypes.c_int64(1)):
+        with pytest.raises(Exception) as e:
+            tp.pack(0, wrong, t, 0, 8, 0, 0)
+        assert not isinstance(e.value, tp.TpError)
