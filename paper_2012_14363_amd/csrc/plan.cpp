@@ -476,13 +476,13 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
         // them (12-byte rows at 13: 46 / 132, 24 at 25: 40 / 71, 64 at 67: 35 / 38), and for rows beyond 1 KiB
         // (2408 bytes at 4096: 24.8 / 27.3); but for rows of half a line and more only beyond 4 MiB, since what L2 still
         // holds when a kernel ends is written then (4 MiB, written through / streaming: 96 at 112 6.0 / 6.7, 128 at 129
-        // 5.9 / 6.7, 1500 at 1501 5.8 / 6.6).
+        // 5.9 / 6.7, 1500 at 1501 5.8 / 6.6) and rows fit the workgroup, one word to a thread.
         const bool streams = bytes > kFillBytes || run < kLineBytes / 2;
         const bool shared_lines = !apart || (inner_pitch >= kLineBytes / 2 && inner_pitch < kLineBytes * 3 / 2 && inner_pitch - run < 32 && streams);
         //   One row per thread, except where rows are so close (or, short ones, so far apart: one address
         // translation each) that four are the better (24 at 25: 40 / 47; 24 at 4096: 13.1 / 16.5).
         ur_short = (run <= 32 && !apart) || (run < 64 && inner_pitch >= kPageBytes) ? 4 : 1;
-        nt = ur_short == 1 && !shared_lines && (run <= 1024 || !streams) ? 7 : 3;
+        nt = ur_short == 1 && !shared_lines && (run <= 1024 || (!streams && run <= kBlockThreads * 16)) ? 7 : 3;
         //   Word.  Rows of at least a line: 16 bytes (200 at 216, words of 8 and of 16: 12.2 and 15.4, 9.3 and 13.3; 192 at 228:
         // 12.8 and 15.4, 9.5 and 13.7), or 8 for rows of at most two lines at odd addresses and 384 bytes or more apart
         // (128 at 768: 14.0 and 20.3, 16.5 and 22.8; 56 MiB, 200 at 384: 21.2 and 39.0, 24.6 and 43.8).
