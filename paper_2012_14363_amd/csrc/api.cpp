@@ -316,14 +316,7 @@ int transfer_batch(bool unpack, int n, const void* const* typed_bufs, const int*
         if (r.size == 0) continue;
         int rc = plan_request(*r.node, counts[i], r.where, &in, &mine);   // fails on no type that could be committed
         if (rc != kSuccess) return rc;
-        for (const Launch& l : mine) {
-            if (!batchable(l)) {
-                singles.push_back(l);
-            } else if (!group.add(l)) {
-                if ((rc = flush()) != kSuccess) return rc;
-                group.add(l);
-            }
-        }
+        if ((rc = add_launches(mine, &group, &singles, flush)) != kSuccess) return rc;
     }
     int rc = flush();
     if (rc == kSuccess) rc = enqueue_launches(singles, unpack, stream);

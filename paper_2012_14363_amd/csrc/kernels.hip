@@ -91,10 +91,9 @@ __global__ void __launch_bounds__(kBlockThreads) tile_kernel(KParams p) {
 // parameters are a BatchDesc, 96 bytes (KParams: 448): above 104 bytes of arguments the runtime's launch was measured to take
 // up to 1.2 us longer on the host (2.6 -> 3.8 us; on other hosts 0.1), which is what bounds calls of up to
 // about 1 MiB.  The grid's size is not read either: it would add 256 bytes of implicit arguments.
-// NRD 0: three row dimensions.
 template <int WLOG2, int UX, int UR, bool UNPACK, int NRD, int NT>
 __global__ void __launch_bounds__(kBlockThreads) tile_kernel(BatchDesc d) {
-    tile_thread<WLOG2, UX, UR, UNPACK, NRD ? NRD : kBatchRowDims>(unpack_desc(d), blockIdx.x, threadIdx.x, DeviceMem<NT>{});
+    compact_thread<WLOG2, UX, UR, UNPACK, NRD>(d, blockIdx.x, threadIdx.x, DeviceMem<NT>{});
 }
 
 // Read-only pass of a staged unpack: plain (cached) loads, so the bytes stay in this XCD's L2.
@@ -189,9 +188,6 @@ struct PickCompact {
     }
 };
 
-// Whether a launch can have its parameters in a BatchDesc.
-bool fits_compact(const Launch& l) { return l.kind == kTile && l.grid == 0 && l.p.nrd <= static_cast<uint32_t>(kBatchRowDims); }
-
 }  // namespace
 
 hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
@@ -210,7 +206,7 @@ hipError_t enqueue(const Launch& l, bool unpack, hipStream_t stream) {
         return launch(prefetch_kernel, grid, stream, f);
     }
     const int nt = l.hints();
-    if (fits_compact(l) && (nt == 2 || nt == 3 || (unpack && nt >= 6 && l.ux == 1 && l.ur == 1))) {
+    if (runs_compact(l, unpack)) {
         void (*small)(BatchDesc) = nullptr;
         if (unpack) {
             PickCompact<true> pick;

@@ -563,6 +563,12 @@ bool batchable(const Launch& l) {
            (l.nt & 4) == 0 && l.grid == 0;
 }
 
+bool runs_compact(const Launch& l, bool unpack) {
+    if (l.kind != kTile || l.grid != 0 || l.p.nrd > static_cast<uint32_t>(kBatchRowDims)) return false;
+    const int nt = l.hints();
+    return nt == 2 || nt == 3 || (unpack && nt >= 6 && l.ux == 1 && l.ur == 1);   // written through: planned with one word per thread alone
+}
+
 BatchDesc compact(const Launch& l) {
     BatchDesc d;
     const KParams& p = l.p;
@@ -619,25 +625,6 @@ void BatchBuilder::finish(BatchParams* out) {
     }
     n_ = 0;
     total_ = 0;
-}
-
-void make_batches(const std::vector<Launch>& launches, std::vector<BatchParams>* batches,
-                  std::vector<Launch>* singles) {
-    BatchBuilder group;
-    auto flush = [&] {
-        if (group.empty()) return;
-        batches->emplace_back();
-        group.finish(&batches->back());
-    };
-    for (const Launch& l : launches) {
-        if (!batchable(l)) {
-            singles->push_back(l);
-        } else if (!group.add(l)) {
-            flush();
-            group.add(l);
-        }
-    }
-    flush();
 }
 
 std::string describe(const std::vector<BatchParams>& batches) {

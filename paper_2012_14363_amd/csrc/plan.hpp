@@ -179,6 +179,9 @@ static_assert(sizeof(BatchParams) <= 4096, "BatchParams must fit the kernel-argu
 
 // True if a launch can ride in a batch (few enough row dimensions).
 bool batchable(const Launch& l);
+// True if a launch of its own gets its parameters as such a descriptor (kernels.hip: tile_kernel(BatchDesc)): one tile per
+// workgroup, at most kBatchRowDims row dimensions, and hints that kernel is built for.
+bool runs_compact(const Launch& l, bool unpack);
 // A row-by-row launch of at most kBatchRowDims row dimensions as such a descriptor.
 BatchDesc compact(const Launch& l);
 
@@ -197,10 +200,21 @@ private:
     BatchDesc desc_[kBatchMax];
 };
 
-// Groups launches into batches of at most kBatchMax descriptors, in order.  Launches that are
-// not batchable are appended to `singles`.
-void make_batches(const std::vector<Launch>& launches, std::vector<BatchParams>* batches,
-                  std::vector<Launch>* singles);
+// Adds a request's launches to the batch being built; those that are not batchable are appended to `singles`.
+// `flush()` finishes and enqueues a batch that is full; a status of its other than success ends this.
+template <class Flush>
+int add_launches(const std::vector<Launch>& launches, BatchBuilder* group, std::vector<Launch>* singles, Flush&& flush) {
+    for (const Launch& l : launches) {
+        if (!batchable(l)) {
+            singles->push_back(l);
+        } else if (!group->add(l)) {
+            const int rc = flush();
+            if (rc != 0) return rc;
+            group->add(l);
+        }
+    }
+    return 0;
+}
 std::string describe(const std::vector<BatchParams>& batches);
 
 // One line per launch, for tp_last_plan().

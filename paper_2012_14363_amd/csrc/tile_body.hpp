@@ -354,6 +354,12 @@ TP_HD inline SmallParams unpack_desc(const BatchDesc& d) {
     return p;
 }
 
+// Thread `tid` of workgroup `block` of a launch whose parameters are a descriptor.  NRD 0: three row dimensions.
+template <int WLOG2, int UX, int UR, bool UNPACK, int NRD, class Mem>
+TP_HD inline void compact_thread(const BatchDesc& d, uint32_t block, uint32_t tid, Mem mem) {
+    tile_thread<WLOG2, UX, UR, UNPACK, NRD ? NRD : kBatchRowDims>(unpack_desc(d), block, tid, mem);
+}
+
 // Index of the descriptor that owns workgroup `block`: the first j with block < block_end[j].
 TP_HD inline uint32_t find_desc(const BatchParams& b, uint32_t block) {
     uint32_t lo = 0, hi = b.n - 1;

@@ -39,6 +39,7 @@ struct Checks {
     bool in_store_pass = false;
     uint32_t tile = 0;
     int64_t misplaced = 0;
+    int64_t compact = 0;    // launches run from a descriptor
 };
 
 struct HostMem {
@@ -92,6 +93,20 @@ struct RunLaunch {
     }
 };
 
+// The same for a launch whose parameters are a descriptor.
+template <bool UNPACK>
+struct RunCompact {
+    tp::BatchDesc d;
+    uint32_t nblocks;
+    HostMem mem;
+    template <int WLOG2, int UX, int UR, int NRD>
+    void operator()() {
+        for (uint32_t b = 0; b < nblocks; ++b)
+            for (uint32_t t = 0; t < static_cast<uint32_t>(tp::kBlockThreads); ++t)
+                tp::compact_thread<WLOG2, UX, UR, UNPACK, NRD>(d, b, t, mem);
+    }
+};
+
 // A transposing launch: per workgroup, every thread's first phase, then every thread's second
 // phase (the barrier), with the workgroup's LDS tile as a host array.  Reports an LDS index
 // outside the tile as an out-of-bounds access.
@@ -132,6 +147,18 @@ bool run_xpose(const tp::Launch& l, bool unpack, HostMem mem) {
     }
 }
 
+// The batches of a batched call: what the library enqueues as each is full, kept in order.
+struct Batches {
+    std::vector<tp::BatchParams>* out;
+    tp::BatchBuilder builder{};
+    int operator()() {
+        if (builder.empty()) return 0;
+        out->emplace_back();
+        builder.finish(&out->back());
+        return 0;
+    }
+};
+
 // Runs one planned launch of either kind; false if it names no kernel variant.
 bool run_launch(const tp::Launch& l, bool unpack, Checks* c) {
     if (l.grid > l.nblocks) return false;
@@ -154,6 +181,16 @@ bool run_launch(const tp::Launch& l, bool unpack, Checks* c) {
         // every 16-byte word of the bytes is loaded exactly once (the last may be pulled back)
         if (c->loads - loads_before != static_cast<int64_t>((f.bytes + 15) / 16)) c->oob++;
         return true;
+    }
+    if (tp::runs_compact(l, unpack)) {   // the launcher's choice
+        c->in_store_pass = false;
+        c->compact++;
+        if (unpack) {
+            RunCompact<true> run{tp::compact(l), l.nblocks, HostMem{c}};
+            return tp::dispatch_launch(l, l.p.nrd, run);
+        }
+        RunCompact<false> run{tp::compact(l), l.nblocks, HostMem{c}};
+        return tp::dispatch_launch(l, l.p.nrd, run);
     }
     const tp::KParams p = tp::kernel_params(l);
     // a launch on few workgroups behind a read-only pass is one of its store passes (a chunk of fewer
@@ -222,6 +259,7 @@ int emul_transfer(int unpack, int ndims, int64_t start, const int64_t* counts, c
     result[4] = c.duplicates;
     result[5] = c.prefetched_hi - c.prefetched_lo;   // span of the packed bytes the read-only passes cover
     result[6] = c.misplaced;
+    result[7] = c.compact;
     return 0;
 }
 
@@ -251,7 +289,9 @@ int64_t emul_plan_only(int unpack, int ndims, int64_t start, const int64_t* coun
     std::vector<tp::BatchParams> batches;
     if (batched) {
         singles.clear();
-        tp::make_batches(planned, &batches, &singles);
+        Batches group{&batches};
+        tp::add_launches(planned, &group.builder, &singles, group);
+        group();
     }
     int64_t n = 0;
     auto put = [&](int64_t tiles, int64_t grid, int64_t rows, int64_t kind) {
@@ -298,8 +338,8 @@ int64_t emul_fastdiv_mismatches(uint32_t small_limit, int64_t random_pairs, uint
 }
 
 // The batched form: n requests (request i: StridedBlock i, extent, object count, origin in the one
-// typed buffer) sharing the packed buffer from `position` on.  Plans every request, groups the
-// launches into batches exactly as the library does, and runs batch_thread for every workgroup
+// typed buffer) sharing the packed buffer from `position` on.  Plans every request, puts its
+// launches into batches by the function the library uses, and runs batch_thread for every workgroup
 // and thread.  result[3] = number of batched launches, result[4] = launches left single,
 // result[5] = destination bytes written again with the same value.
 int emul_transfer_batch(int unpack, int n, const int* ndims, const int64_t* starts, const int64_t* counts,
@@ -307,7 +347,9 @@ int emul_transfer_batch(int unpack, int n, const int* ndims, const int64_t* star
                         const int64_t* origins, const int64_t* sizes, char* typed_buf, int64_t typed_len,
                         char* packed_buf, int64_t packed_len, int64_t position, uint8_t* write_count,
                         int64_t* result) {
-    std::vector<tp::Launch> launches;
+    std::vector<tp::BatchParams> batches;
+    std::vector<tp::Launch> singles;
+    Batches group{&batches};
     int64_t pos = position;
     for (int i = 0; i < n; ++i) {
         tp::PlanInput in;
@@ -326,12 +368,10 @@ int emul_transfer_batch(int unpack, int n, const int* ndims, const int64_t* star
         std::vector<tp::Launch> mine;
         const int rc = tp::plan_launches(in, &mine);
         if (rc != tp::kSuccess) return rc;
-        launches.insert(launches.end(), mine.begin(), mine.end());
+        tp::add_launches(mine, &group.builder, &singles, group);
         pos += objects[i] * sizes[i];
     }
-    std::vector<tp::BatchParams> batches;
-    std::vector<tp::Launch> singles;
-    tp::make_batches(launches, &batches, &singles);
+    group();
     Checks c{typed_buf, typed_buf + typed_len, packed_buf, packed_buf + packed_len, write_count,
              unpack ? typed_buf : packed_buf};
     for (const tp::BatchParams& b : batches)

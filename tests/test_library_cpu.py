@@ -309,6 +309,43 @@ def test_emulated_tile_shapes(a0):
     _emulate_roundtrip(vector(37, a0, a0 + 16, BYTE), 1)
 
 
+#: run, pitch, rows, further dimension (count, stride), typed offset: requests large enough for the planner's rules for many rows
+MANY_ROWS = [(1, 8, 1100000, None, 3), (3, 64, 350001, None, 5), (7, 56, 160000, None, 1), (8, -128, 140001, None, 2),
+             (12, 13, 90001, None, 1), (24, 600, 44000, None, 7), (33, 63, 33001, None, 0), (64, 192, 17001, None, 64),
+             (100, 512, 105, (101, 512 * 107), 4), (127, 150, 9001, None, 3), (130, 4096, 50, (165, 4096 * 51), 1),
+             (200, 216, 149, (37, -216 * 150), 5), (500, 512, 8500, None, 0), (512, 1024, 8300, None, 0),
+             (1025, 1058, 4200, None, 2), (2408, 2648, 90, (20, 2648 * 91), 40), (4100, 4200, 300, None, 1), (1 << 20, 1 << 20, 5, None, 3)]
+
+
+@pytest.mark.parametrize("run,pitch,rows,outer,offset", MANY_ROWS)
+def test_emulated_many_rows(run, pitch, rows, outer, offset):
+    """Launches of a MiB and more as the GPU runs them, from a descriptor: within bounds and equal to the oracle, both ways."""
+    recipe = hvector(rows, 1, pitch, contiguous(run, BYTE))
+    if outer:
+        recipe = hvector(outer[0], 1, outer[1], recipe)
+    h = tp.type_from_recipe(recipe)
+    block, (lb, extent), size = tp.type_get_strided_block(h), tp.type_get_extent(h), tp.type_size(h)
+    tp.type_free(h)
+    origin = offset - min(lb, 0)
+    store = np.zeros(extent + offset + 192, np.uint8)
+    base = (-store.ctypes.data) % 128
+    typed = store[base:base + extent + offset]
+    typed[:] = W.random_bytes(run, typed.size)
+    packed, want = np.full(size + 3, 0xEE, np.uint8), np.full(size + 3, 0xEE, np.uint8)
+    res = host_emul.transfer(False, block, extent, 1, typed, origin, packed, 3)
+    assert (res["rc"], res["oob"], res["rewritten"]) == (0, 0, 0), res["plan"]
+    assert res["compact"] == res["launches"] == 1, res["plan"]
+    cc.pack(typed, origin, 1, recipe, want, 3)
+    assert np.array_equal(packed, want), res["plan"]
+    packed[:] = W.random_bytes(pitch & 0xffff, packed.size)
+    want = typed.copy()
+    res = host_emul.transfer(True, block, extent, 1, typed, origin, packed, 3)
+    assert (res["rc"], res["oob"], res["rewritten"]) == (0, 0, 0), res["plan"]
+    assert res["compact"] == res["launches"] == 1, res["plan"]
+    cc.unpack(packed, 3, want, origin, 1, recipe)
+    assert np.array_equal(typed, want), res["plan"]
+
+
 def test_emulated_word_width_follows_run_length_only():
     # 16-byte words wherever a run holds 16 bytes, at any address and for any run length or stride
     t = vector(16, 64, 128, BYTE)
