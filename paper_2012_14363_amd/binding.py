@@ -297,14 +297,13 @@ class Batch:
     def __init__(self, typed_bufs, counts, types):
         n = len(types)
         assert len(typed_bufs) == len(counts) == n
-        self.n = n
-        self.ptrs = (ctypes.c_void_p * n)(*[_ptr(b) for b in typed_bufs])
-        self.counts = (ctypes.c_int * n)(*counts)
-        self.types = (ctypes.c_int32 * n)(*types)
+        held = ((ctypes.c_void_p * n)(*[_ptr(b) for b in typed_bufs]), (ctypes.c_int * n)(*counts), (ctypes.c_int32 * n)(*types))
+        # raw: what _pycall reads, made here so that the first call need not
+        self.__dict__.update(n=n, ptrs=held[0], counts=held[1], types=held[2], raw=(n, *map(ctypes.addressof, held), held))
 
     def __setattr__(self, name, value):
         super().__setattr__(name, value)
-        self.__dict__["raw"] = None   # what _pycall reads: _marshal makes it when the next call asks
+        self.__dict__["raw"] = None   # _marshal makes it anew when the next call asks
 
     def __delattr__(self, name):
         super().__delattr__(name)
