@@ -524,11 +524,12 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
         // One word per thread, and so more and shorter workgroups, once there are enough of them to fill the
         // chip several times over: for long runs (64 MiB, us, against four words per thread: dense 24.2 -> 23.7, 1000 bytes at
         // 1024: 25.1 -> 23.8, 2408 at 4096: 28.3 -> 24.3, 9000 at 12288: 27.2 -> 24.5), and when packing from
-        // rows far apart (100 at 512: 27.9 -> 26.3), short ones where their distance is a multiple of 512 bytes (12 at 512: 46 ->
-        // 42, 32 at 512: 52 -> 47; but 20 at 1000: 30.3 -> 31.5); short rows close together want the four (24 at 64: 39 / 55).
+        // rows far apart (100 at 512: 27.9 -> 26.3), short ones where their distance is a power of two from 512 bytes on (12 at
+        // 512: 46 -> 42, 32 at 512: 52 -> 47; but 20 at 1000: 30.3 -> 31.5, 64 MiB of 8 at 1536: 195 -> 219); short rows
+        // close together want the four (24 at 64: 39 / 55).
         if (tuned && bytes > kFillBytes && !revisits) {
             const bool apart = inner_pitch >= 2 * kLineBytes && inner_pitch >= 2 * run;
-            if (run >= 512 || in.unpack || (apart && (run >= 64 || (inner_pitch % 512 == 0 && inner_pitch < kPageBytes)))) ur_short = 1;
+            if (run >= 512 || in.unpack || (apart && (run >= 64 || (inner_pitch >= 512 && inner_pitch < kPageBytes && (inner_pitch & (inner_pitch - 1)) == 0)))) ur_short = 1;
             // whole-line rows written through as well: 128 at 512 24.8 -> 23.8, 512 at 1024 24.6 -> 24.0
             if (in.unpack && !partial_rows && dims.size() > 1 && run <= 512) nt = 7;
         }

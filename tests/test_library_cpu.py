@@ -602,6 +602,13 @@ def test_every_launch_fits_the_grid_limit():
     assert seen_capped
 
 
+def test_rows_per_thread_of_short_rows_packed_from_far_apart():
+    # 60-byte rows, 16-byte words, 64 rows to a workgroup: one row per thread at powers of two from 512 bytes on, else four
+    for pitch, per_thread in ((256, 4), (512, 1), (1024, 1), (1536, 4), (2048, 1), (2560, 4), (3584, 4), (4096, 4)):
+        launch, = host_emul.plan_only(False, (0, [60, 1 << 17], [1, pitch]), 60, 1)
+        assert launch["tiles"] == (1 << 17) // (64 * per_thread), (pitch, launch)
+
+
 def test_override_keys_take_what_the_header_documents():
     # every key and value include/tp_pack.h lists is accepted, a few it does not list are refused,
     # and each key is put back to its default
