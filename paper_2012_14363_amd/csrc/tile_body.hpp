@@ -201,6 +201,54 @@ TP_HD inline char* xpose_packed(const XParams& p, const XposeOrigin& g, uint32_t
            (static_cast<int64_t>(static_cast<uint64_t>(b) * p.ew + w) << WLOG2);
 }
 
+// A thread's share of a phase: words of tile rows slow0, slow0 + rows_per_pass, ..., each `lanes` words at a time.
+// kWhole: the tile lies inside the matrix, so there is nothing to check.  Tile rows go in groups of kGroup: all of a group's
+// loads are issued before its first store, so that many memory accesses are in flight per thread.
+// (By value when packing and by reference when unpacking: the compiler allocates registers by it.  As a lambda of xpose_phase, which is
+// by reference, packing thin matrices and 12-byte elements took 5 to 10 % longer than by value, 1.4 M x 9 of 2 bytes 33.0 us against
+// 30.4, 2048 x 2048 of 12 bytes 35.0 / 32.6; by value, unpacking 1-byte elements 5 to 14 %, 4.2 M x 6 41.8 / 37.8.)
+template <bool UNPACK, class T>
+using XposeArg = typename std::conditional<UNPACK, const T&, T>::type;
+template <int WLOG2, bool UNPACK, bool LOAD, bool kWhole, uint32_t kGroup, class Mem>
+TP_HD inline void xpose_move(const XParams& p, const XposeOrigin& g, XposeArg<UNPACK, uint32_t> tid, XposeArg<UNPACK, uint32_t> slow0,
+                             XposeArg<UNPACK, uint32_t> lanes, XposeArg<UNPACK, uint32_t> rows_per_pass, XposeArg<UNPACK, uint32_t> te_fast,
+                             XposeArg<UNPACK, uint32_t> te_slow, XposeArg<UNPACK, uint32_t> ew, XposeArg<UNPACK, uint32_t> pitch,
+                             XposeArg<UNPACK, Mem> mem, XposeArg<UNPACK, typename WordOf<WLOG2>::type*> lds) {
+    constexpr bool kTypedSide = UNPACK != LOAD;
+    using W = typename WordOf<WLOG2>::type;
+    // Tile rows longer than the lanes along them (thin tiles grown along the other dimension) are
+    // walked in chunks of `lanes` words.
+    for (uint32_t fast = tid & (lanes - 1u); fast < te_fast * ew; fast += lanes) {
+        const uint32_t fe = ew == 1 ? fast : fast / ew;  // element and word within it along the fast dimension
+        const uint32_t fw = fast - fe * ew;
+        for (uint32_t first = slow0; first < te_slow; first += kGroup * rows_per_pass) {
+            W v[kGroup];
+            bool ok[kGroup];
+            W* cell[kGroup];
+            char* far[kGroup];
+#pragma unroll
+            for (uint32_t k = 0; k < kGroup; ++k) {
+                const uint32_t slow = first + k * rows_per_pass;
+                const uint32_t la = kTypedSide ? fe : slow, lb = kTypedSide ? slow : fe;
+                const uint32_t a = g.a0 + la, b = g.b0 + lb;
+                ok[k] = kWhole || (slow < te_slow && a < p.ca && b < p.cb);
+                // lanes with nothing to move address the tile's first element, which always exists
+                const uint32_t sa = ok[k] ? a : g.a0, sb = ok[k] ? b : g.b0, sw = ok[k] ? fw : 0u;
+                cell[k] = lds + (ok[k] ? lb * pitch + la * ew + fw : 0u);
+                far[k] = kTypedSide ? const_cast<char*>(xpose_typed<WLOG2>(p, g, sa, sb, sw)) : xpose_packed<WLOG2>(p, g, sa, sb, sw);
+                if (LOAD) v[k] = mem.template load<W>(far[k]);
+                else if (ok[k]) v[k] = *cell[k];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kGroup; ++k) {
+                if (!ok[k]) continue;
+                if (LOAD) *cell[k] = v[k];
+                else mem.template store<W>(far[k], v[k]);
+            }
+        }
+    }
+}
+
 // One phase of thread `tid`.  LOAD: read the tile from the source side into LDS; else write it from
 // LDS to the destination side.  Lanes run along the dimension that is contiguous on that side (A
 // on the typed side, B on the packed side), one word each; the tile lives in LDS as
@@ -211,7 +259,6 @@ TP_HD inline char* xpose_packed(const XParams& p, const XposeOrigin& g, uint32_t
 template <int WLOG2, bool UNPACK, bool LOAD, bool SQUARE, class Mem>
 TP_HD inline void xpose_phase(const XParams& p, uint32_t block, uint32_t tid, Mem mem,
                               typename WordOf<WLOG2>::type* lds) {
-    using W = typename WordOf<WLOG2>::type;
     const XposeOrigin g = xpose_origin(p, block);
     // the typed side is this phase's side when packing and loading, or unpacking and storing
     constexpr bool kTypedSide = UNPACK != LOAD;
@@ -223,64 +270,26 @@ TP_HD inline void xpose_phase(const XParams& p, uint32_t block, uint32_t tid, Me
     const uint32_t te_slow = SQUARE ? kEdge : kTypedSide ? p.te_b : p.te_a;
     const uint32_t rows_per_pass = static_cast<uint32_t>(kBlockThreads) >> f_log2;
     const uint32_t lanes = 1u << f_log2, slow0 = tid >> f_log2;
-    // whole: the tile lies inside the matrix, so there is nothing to check.
-    auto move = [&](auto whole, auto group) {
-        constexpr bool kWhole = decltype(whole)::value;
-        // Tile rows in groups of kGroup: all of a group's loads are issued before its first store,
-        // so that many memory accesses are in flight per thread.
-        constexpr uint32_t kGroup = decltype(group)::value;
-        // Tile rows longer than the lanes along them (thin tiles grown along the other dimension) are
-        // walked in chunks of `lanes` words.
-        for (uint32_t fast = tid & (lanes - 1u); fast < te_fast * ew; fast += lanes) {
-            const uint32_t fe = ew == 1 ? fast : fast / ew;  // element and word within it along the fast dimension
-            const uint32_t fw = fast - fe * ew;
-            for (uint32_t first = slow0; first < te_slow; first += kGroup * rows_per_pass) {
-                W v[kGroup];
-                bool ok[kGroup];
-                W* cell[kGroup];
-                char* far[kGroup];
-#pragma unroll
-                for (uint32_t k = 0; k < kGroup; ++k) {
-                    const uint32_t slow = first + k * rows_per_pass;
-                    const uint32_t la = kTypedSide ? fe : slow, lb = kTypedSide ? slow : fe;
-                    const uint32_t a = g.a0 + la, b = g.b0 + lb;
-                    ok[k] = kWhole || (slow < te_slow && a < p.ca && b < p.cb);
-                    // lanes with nothing to move address the tile's first element, which always exists
-                    const uint32_t sa = ok[k] ? a : g.a0, sb = ok[k] ? b : g.b0, sw = ok[k] ? fw : 0u;
-                    cell[k] = lds + (ok[k] ? lb * pitch + la * ew + fw : 0u);
-                    far[k] = kTypedSide ? const_cast<char*>(xpose_typed<WLOG2>(p, g, sa, sb, sw)) : xpose_packed<WLOG2>(p, g, sa, sb, sw);
-                    if (LOAD) v[k] = mem.template load<W>(far[k]);
-                    else if (ok[k]) v[k] = *cell[k];
-                }
-#pragma unroll
-                for (uint32_t k = 0; k < kGroup; ++k) {
-                    if (!ok[k]) continue;
-                    if (LOAD) *cell[k] = v[k];
-                    else mem.template store<W>(far[k], v[k]);
-                }
-            }
-        }
-    };
-    using Few = std::integral_constant<uint32_t, 4>;
-    using Some = std::integral_constant<uint32_t, 8>;
-    using Many = std::integral_constant<uint32_t, 16>;
+#define TP_XPOSE_MOVE(WHOLE, GROUP) \
+    xpose_move<WLOG2, UNPACK, LOAD, WHOLE, GROUP, Mem>(p, g, tid, slow0, lanes, rows_per_pass, te_fast, te_slow, ew, pitch, mem, lds)
     if constexpr (SQUARE) {
         // a thread's rows: 64, 16 or 4 of a tile of edge 128, 64 or 32
-        using Group = typename std::conditional<kEdgeLog2 == 5, Few, Many>::type;
+        constexpr uint32_t kGroup = kEdgeLog2 == 5 ? 4 : 16;
         // The checked form for all tiles of a ragged matrix of 4- or 8-byte elements that is being unpacked: its whole tiles gain
         // less than the cut ones behind them lose to the second form (checked / both, sources from HBM, us: 4-byte elements 1500 x
         // 1400 8.8 / 10.0, 8000 x 700 15.0 / 16.6, 8-byte 1500 x 1400 9.8 / 12.0; 1-byte 16.6 / 13.3 at 300 x 300).
         const bool checked = UNPACK && (WLOG2 == 2 || WLOG2 == 3) && ((p.ca | p.cb) & (kEdge - 1u)) != 0;
-        if (!checked && p.ca - g.a0 >= kEdge && p.cb - g.b0 >= kEdge) move(std::true_type{}, Group{});
-        else move(std::false_type{}, Group{});
+        if (!checked && p.ca - g.a0 >= kEdge && p.cb - g.b0 >= kEdge) TP_XPOSE_MOVE(true, kGroup);
+        else TP_XPOSE_MOVE(false, kGroup);
     } else {
         // Groups no larger than a thread's rows need: the rest of a group would load the tile's first element (3 M records
         // of six 4-byte fields from field arrays, six rows to a thread, groups of 16 -> 8: 44.9 -> 33.5 us).
         const uint32_t passes = (te_slow + rows_per_pass - 1) >> (8 - f_log2);
-        if (passes <= 4) move(std::false_type{}, Few{});
-        else if (passes <= 8) move(std::false_type{}, Some{});
-        else move(std::false_type{}, Many{});
+        if (passes <= 4) TP_XPOSE_MOVE(false, 4);
+        else if (passes <= 8) TP_XPOSE_MOVE(false, 8);
+        else TP_XPOSE_MOVE(false, 16);
     }
+#undef TP_XPOSE_MOVE
 }
 
 // Calls f.template operator()<WLOG2, UX, UR, NRD>() for the variant a launch names;
