@@ -79,46 +79,46 @@ def sector_bound_fraction(run: int, granule: int = 128) -> float:
 # Keyed by (op, a0): the plan the call had when the counters were read (tp_last_plan, summarised), bytes
 # fetched, bytes written.  A point whose plan differs today reports no traffic rather than a stale one.
 MEASURED_TRAFFIC = {
-    ('pack', 1): {"plan": 'tile W=1 ux=1 ur=4 nt=3 bx=1 n0=1 back=0 rows=67108864 nrd=1 blocks=65536',
-                   "fetch": 8585916908, "write": 72429112},
-    ('pack', 2): {"plan": 'tile W=1 ux=1 ur=4 nt=3 bx=2 n0=2 back=0 rows=33554432 nrd=1 blocks=65536',
-                   "fetch": 4293019034, "write": 72044646},
-    ('pack', 4): {"plan": 'tile W=1 ux=1 ur=4 nt=3 bx=4 n0=4 back=0 rows=16777216 nrd=1 blocks=65536',
-                   "fetch": 2146530243, "write": 70420976},
-    ('pack', 8): {"plan": 'tile W=2 ux=1 ur=4 nt=3 bx=4 n0=4 back=0 rows=8388608 nrd=1 blocks=32768',
-                   "fetch": 1073278299, "write": 67045053},
-    ('pack', 16): {"plan": 'tile W=4 ux=1 ur=4 nt=3 bx=4 n0=4 back=0 rows=4194304 nrd=1 blocks=16384',
-                   "fetch": 536656485, "write": 67083416},
-    ('pack', 32): {"plan": 'tile W=4 ux=1 ur=4 nt=3 bx=8 n0=8 back=0 rows=2097152 nrd=1 blocks=16384',
-                   "fetch": 268343084, "write": 67062956},
-    ('pack', 64): {"plan": 'tile W=16 ux=1 ur=4 nt=3 bx=4 n0=4 back=0 rows=1048576 nrd=1 blocks=4096',
-                   "fetch": 134187918, "write": 67143391},
-    ('pack', 128): {"plan": 'tile W=16 ux=1 ur=4 nt=3 bx=8 n0=8 back=0 rows=524288 nrd=1 blocks=4096',
-                   "fetch": 67110143, "write": 67115769},
-    ('pack', 256): {"plan": 'tile W=16 ux=1 ur=4 nt=3 bx=16 n0=16 back=0 rows=262144 nrd=1 blocks=4096',
-                   "fetch": 67109888, "write": 67113595},
-    ('pack', 512): {"plan": 'tile W=16 ux=4 ur=1 nt=3 bx=256 n0=4194304 back=0 rows=1 nrd=0 blocks=4096',
+    ('pack', 1): {"plan": 'tile W=1 ux=1 ur=1 nt=3 bx=1 n0=1 back=0 rows=67108864 nrd=1 blocks=262144',
+                   "fetch": 8586726664, "write": 74668033},
+    ('pack', 2): {"plan": 'tile W=1 ux=1 ur=1 nt=3 bx=2 n0=2 back=0 rows=33554432 nrd=1 blocks=262144',
+                   "fetch": 4293416208, "write": 71560659},
+    ('pack', 4): {"plan": 'tile W=1 ux=1 ur=1 nt=3 bx=4 n0=4 back=0 rows=16777216 nrd=1 blocks=262144',
+                   "fetch": 2146683121, "write": 71366233},
+    ('pack', 8): {"plan": 'tile W=2 ux=1 ur=1 nt=3 bx=4 n0=4 back=0 rows=8388608 nrd=1 blocks=131072',
+                   "fetch": 1073359442, "write": 67062880},
+    ('pack', 16): {"plan": 'tile W=4 ux=1 ur=1 nt=3 bx=4 n0=4 back=0 rows=4194304 nrd=1 blocks=65536',
+                   "fetch": 536692164, "write": 67062880},
+    ('pack', 32): {"plan": 'tile W=4 ux=1 ur=1 nt=3 bx=8 n0=8 back=0 rows=2097152 nrd=1 blocks=65536',
+                   "fetch": 268358813, "write": 67062880},
+    ('pack', 64): {"plan": 'tile W=16 ux=1 ur=1 nt=3 bx=4 n0=4 back=0 rows=1048576 nrd=1 blocks=16384',
+                   "fetch": 134192394, "write": 67128115},
+    ('pack', 128): {"plan": 'tile W=16 ux=1 ur=1 nt=3 bx=8 n0=8 back=0 rows=524288 nrd=1 blocks=16384 keep',
+                   "fetch": 67108864, "write": 67131249},
+    ('pack', 256): {"plan": 'tile W=16 ux=1 ur=1 nt=3 bx=16 n0=16 back=0 rows=262144 nrd=1 blocks=16384 keep',
+                   "fetch": 67108864, "write": 67154593},
+    ('pack', 512): {"plan": 'tile W=16 ux=1 ur=1 nt=3 bx=256 n0=4194304 back=0 rows=1 nrd=0 blocks=16384 keep',
                    "fetch": 67108864, "write": 67108864},
     ('unpack', 1): {"plan": '4 x [prefetch bytes=16777216 tile=256 blocks=65536 grid=1536] + 4 x [tile W=1 ux=1 ur=1 nt=6 bx=1 n0=1 back=0 rows=16777216 nrd=1 blocks=65536 grid=192]',
-                   "fetch": 134391726, "write": 2145441687},
+                   "fetch": 134449064, "write": 2146012145},
     ('unpack', 2): {"plan": '4 x [prefetch bytes=16777216 tile=512 blocks=32768 grid=1536] + 4 x [tile W=2 ux=1 ur=1 nt=6 bx=1 n0=1 back=0 rows=8388608 nrd=1 blocks=32768 grid=192]',
-                   "fetch": 134391726, "write": 1072720844},
+                   "fetch": 134449064, "write": 1073006072},
     ('unpack', 4): {"plan": '4 x [prefetch bytes=16777216 tile=1024 blocks=16384 grid=1536] + 4 x [tile W=4 ux=1 ur=1 nt=6 bx=1 n0=1 back=0 rows=4194304 nrd=1 blocks=16384 grid=192]',
-                   "fetch": 134391726, "write": 536360422},
+                   "fetch": 134449064, "write": 536503036},
     ('unpack', 8): {"plan": '4 x [prefetch bytes=16777216 tile=2048 blocks=8192 grid=1536] + 4 x [tile W=8 ux=1 ur=1 nt=6 bx=1 n0=1 back=0 rows=2097152 nrd=1 blocks=8192 grid=192]',
-                   "fetch": 134391726, "write": 268180211},
+                   "fetch": 134449064, "write": 268251518},
     ('unpack', 16): {"plan": '4 x [prefetch bytes=16777216 tile=4096 blocks=4096 grid=1536] + 4 x [tile W=16 ux=1 ur=1 nt=6 bx=1 n0=1 back=0 rows=1048576 nrd=1 blocks=4096 grid=192]',
-                   "fetch": 134334409, "write": 134090105},
-    ('unpack', 32): {"plan": 'tile W=4 ux=1 ur=1 nt=7 bx=8 n0=8 back=0 rows=2097152 nrd=1 blocks=65536',
-                   "fetch": 67102723, "write": 67045053},
-    ('unpack', 64): {"plan": 'tile W=8 ux=1 ur=1 nt=7 bx=8 n0=8 back=0 rows=1048576 nrd=1 blocks=32768',
-                   "fetch": 67096582, "write": 67045053},
-    ('unpack', 128): {"plan": 'tile W=16 ux=1 ur=4 nt=3 bx=8 n0=8 back=0 rows=524288 nrd=1 blocks=4096',
-                   "fetch": 67104770, "write": 67144926},
-    ('unpack', 256): {"plan": 'tile W=16 ux=1 ur=4 nt=3 bx=16 n0=16 back=0 rows=262144 nrd=1 blocks=4096',
-                   "fetch": 67104898, "write": 67110910},
-    ('unpack', 512): {"plan": 'tile W=16 ux=4 ur=1 nt=3 bx=256 n0=4194304 back=0 rows=1 nrd=0 blocks=4096',
-                   "fetch": 67100676, "write": 67120117},
+                   "fetch": 134449128, "write": 134125759},
+    ('unpack', 32): {"plan": 'tile W=2 ux=1 ur=1 nt=7 bx=16 n0=16 back=0 rows=2097152 nrd=1 blocks=131072 keep',
+                   "fetch": 67108992, "write": 67062880},
+    ('unpack', 64): {"plan": 'tile W=8 ux=1 ur=1 nt=7 bx=8 n0=8 back=0 rows=1048576 nrd=1 blocks=32768 keep',
+                   "fetch": 67108864, "write": 67062880},
+    ('unpack', 128): {"plan": 'tile W=16 ux=1 ur=1 nt=7 bx=8 n0=8 back=0 rows=524288 nrd=1 blocks=16384 keep',
+                   "fetch": 67105793, "write": 67062880},
+    ('unpack', 256): {"plan": 'tile W=16 ux=1 ur=1 nt=7 bx=16 n0=16 back=0 rows=262144 nrd=1 blocks=16384 keep',
+                   "fetch": 67105793, "write": 67062880},
+    ('unpack', 512): {"plan": 'tile W=16 ux=1 ur=1 nt=3 bx=256 n0=4194304 back=0 rows=1 nrd=0 blocks=16384 keep',
+                   "fetch": 67108864, "write": 67110399},
 }
 
 

@@ -535,9 +535,11 @@ int plan_launches(const PlanInput& in, std::vector<Launch>* out) {
         }
     }
     // Loads without the streaming hint leave the source in the Infinity Cache, where the next reader finds it: worth it
-    // while the source is a small part of its 256 MiB.  Measured with three 64 MiB sources in turn (they all
-    // stay): packing and unpacking dense rows 22.7 -> 19.2 us, 100-byte rows at 512 25.4 -> 23.3 and 39.9 -> 34.3;
-    // with twelve (none stays) 23.7 -> 24.1, 26.4 -> 27.3, 39.9 -> 41.2.
+    // while the source is a small part of its 256 MiB.  By what ran before, plain against streaming loads (time ratio over 13 shapes
+    // of rows of half their pitch or more, pack / unpack): source just written on a cache full of other data, 16 MiB 0.91 / 0.88, 56 MiB
+    // 0.81 / 0.78; read again unchanged 0.99 / 0.97, 0.92 / 0.89; from HBM, the cache full of clean lines 1.00 / 0.99, 1.01 / 1.00; from
+    // HBM, the cache full of lines other kernels wrote, which what is kept has to push out, 1.26 / 1.20, 1.28 / 1.33.  What is
+    // packed has usually just been computed, and what is unpacked received.
     bool keep = false;
     if (in.nt < 0 && !(in.unpack && in.packed_on_host)) {
         int64_t footprint = bytes;   // of the source, in whole memory lines
